@@ -662,7 +662,10 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
   float* shift = (float*)(base + plan.o_shift);
   float* scale = (float*)(base + plan.o_scale);
   float* vals_t = (float*)(base + plan.o_vals);
-  e = mls::launch_stage(d_values, n, d, pmin, pmax, shift, scale, vals_t, s);
+  // point-major for the Gaussian, whose tiles gather the points in reach;
+  // attribute-major for the cell list
+  e = mls::launch_stage(d_values, n, d, pmin, pmax, shift, scale, vals_t,
+                        weight->kind != MLS_W_WENDLAND_C2, s);
   if (e != hipSuccess) return device_fail(e, "staging kernel launch");
   tr.mark("stage");
   tr.set_form(mls::lp_use_shape_form(a.degree, d, fp16, weight->kind, d_grad != nullptr, terms,

@@ -52,9 +52,9 @@ struct CellGeom;
 struct LPCells;
 
 // 16-bit matrix-core fit (bf16 or fp16 feature terms, float32
-// accumulation).  vals_t/shift/scale come from launch_stage; the Wendland
-// weight needs `cells`.
-hipError_t launch_fit_lp(const FitArgs& a, const float* vals_t, const float* shift,
+// accumulation).  vals_s/shift/scale come from launch_stage (point-major);
+// the Wendland weight takes its values from `cells` instead.
+hipError_t launch_fit_lp(const FitArgs& a, const float* vals_s, const float* shift,
                          const float* scale, bool fp16, int terms, const LPCells* cells,
                          hipStream_t stream);
 // Attribute slabs of the 16-bit kernel: `forced_ds` attributes per slab
@@ -87,8 +87,8 @@ struct LPBatchClass {
 bool lp_batch_class(const FitArgs& a, bool fp16, int terms, LPBatchClass* cls);
 // The kernel parameters of one request (lp_params_bytes() bytes, opaque).
 size_t lp_params_bytes();
-void lp_params_write(const FitArgs& a, const float* vals_t, const float* shift,
-                     const float* scale, void* out);
+void lp_params_write(const FitArgs& a, const float* vals_s, const float* shift,
+                     const float* scale, bool fp16, void* out);
 // d_items: n_items (request, block) pairs of uint32; d_total[n_req] items
 // per request; d_head (one word), d_done[n_req] and d_skipped[n_req] zero
 // at launch; h_complete (set to 1, or 2 if items were skipped) and h_cancel
@@ -108,10 +108,11 @@ int lp_max_slab(int degree);
 double lp_tile_extent(double dx, double dy, double h);
 
 // Attribute staging: partial ranges (stage_partial_blocks(n) x D floats in
-// pmin and pmax), shift/scale [D], attribute-major normalised copy [D][n].
+// pmin and pmax), shift/scale [D], and the normalised copy, point-major
+// [n][D] (`rows`, the dense weights) or attribute-major [D][n].
 int64_t stage_partial_blocks(int64_t n);
 hipError_t launch_stage(const float* vals, int64_t n, int D, float* pmin, float* pmax,
-                        float* shift, float* scale, float* vals_t, hipStream_t s);
+                        float* shift, float* scale, float* vals_s, bool rows, hipStream_t s);
 
 // Geometry shared by the cell list and the kernels that walk it: square
 // cells of side `cell` from (ox, oy); node tiles of kTileCols x kTileRows

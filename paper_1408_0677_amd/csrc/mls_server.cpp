@@ -417,14 +417,14 @@ void launch_batch(mls_server* s, int si, const std::vector<uint64_t>& members) {
     off += align256(plan.total);
     float* shift = (float*)(b + plan.o_shift);
     float* scale = (float*)(b + plan.o_scale);
-    float* vals_t = (float*)(b + plan.o_vals);
+    float* vals_s = (float*)(b + plan.o_vals);
     if (mls::launch_stage(ps.vals, ps.n, ps.d, (float*)(b + plan.o_pmin),
-                          (float*)(b + plan.o_pmax), shift, scale, vals_t, sl.stream) !=
+                          (float*)(b + plan.o_pmax), shift, scale, vals_s, true, sl.stream) !=
         hipSuccess) {
       ok = false;
       break;
     }
-    mls::lp_params_write(k.args, vals_t, shift, scale,
+    mls::lp_params_write(k.args, vals_s, shift, scale, k.req.precision == MLS_PREC_FP16,
                          sl.desc + L.params + j * mls::lp_params_bytes());
     totals[j] = (uint32_t)k.bc.blocks;
     for (int64_t blk = 0; blk < k.bc.blocks; ++blk) {

@@ -7,9 +7,17 @@
 // (the fit of a f + b is a fit(f) + b: Eq. 5-8 are linear in q and reproduce
 // constants), so the solve maps the result back exactly.
 //
-// The staged payload is attribute-major, vals_t[d][i] = f'_{i,d} (float32),
-// so a workgroup reading a chunk of points of one attribute reads one
-// contiguous run.  Bound: HBM (one read of values, one write).
+// The staged payload (float32) is point-major, vals[i][d] = f'_{i,d}, for the
+// dense weights, whose tiles gather the points in their reach: a point's
+// attributes are one run, so a gathered point costs one or two cache lines
+// (attribute-major it cost a line per attribute).  The compact-support fit
+// takes it attribute-major, vals_t[d][i], and sorts each row into cell order
+// (mls_cells.hip).  Bound: HBM (one read of values, one write).
+//
+// An attribute with a NaN takes a NaN shift and scale: the NaN reaches every
+// node of its field, as it does when all points are summed (0 x NaN), also
+// where the tile never meets the point.  An infinite value does so by itself
+// (an infinite range).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -21,6 +29,14 @@ namespace {
 
 constexpr int kRowsPerBlock = 1024;
 
+// min and max that return NaN when either operand is one.
+__device__ __forceinline__ float nan_min(float a, float b) {
+  return a != a || b != b ? a + b : fminf(a, b);
+}
+__device__ __forceinline__ float nan_max(float a, float b) {
+  return a != a || b != b ? a + b : fmaxf(a, b);
+}
+
 // Partial min / max of each attribute over a block of rows.  Block (32, 8):
 // threadIdx.x walks 32 consecutive attributes of a row (coalesced),
 // threadIdx.y strides over the block's rows.
@@ -30,12 +46,13 @@ __global__ __launch_bounds__(256) void attr_range_kernel(const float* vals, int6
   const int d = blockIdx.y * 32 + threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlock;
   const int64_t r1 = r0 + kRowsPerBlock < n ? r0 + kRowsPerBlock : n;
+  // min and max that keep a NaN once they have met one
   float lo = INFINITY, hi = -INFINITY;
   if (d < D) {
     for (int64_t r = r0 + threadIdx.y; r < r1; r += 8) {
       const float v = vals[r * D + d];
-      lo = fminf(lo, v);
-      hi = fmaxf(hi, v);
+      lo = nan_min(lo, v);
+      hi = nan_max(hi, v);
     }
   }
   smin[threadIdx.y][threadIdx.x] = lo;
@@ -43,8 +60,8 @@ __global__ __launch_bounds__(256) void attr_range_kernel(const float* vals, int6
   __syncthreads();
   if (threadIdx.y == 0 && d < D) {
     for (int q = 1; q < 8; ++q) {
-      lo = fminf(lo, smin[q][threadIdx.x]);
-      hi = fmaxf(hi, smax[q][threadIdx.x]);
+      lo = nan_min(lo, smin[q][threadIdx.x]);
+      hi = nan_max(hi, smax[q][threadIdx.x]);
     }
     pmin[(int64_t)blockIdx.x * D + d] = lo;
     pmax[(int64_t)blockIdx.x * D + d] = hi;
@@ -61,13 +78,13 @@ __global__ __launch_bounds__(256) void attr_finalize_kernel(const float* pmin, c
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   float lo = INFINITY, hi = -INFINITY;
   for (int b = t; b < nblk; b += 256) {
-    lo = fminf(lo, pmin[(int64_t)b * D + d]);
-    hi = fmaxf(hi, pmax[(int64_t)b * D + d]);
+    lo = nan_min(lo, pmin[(int64_t)b * D + d]);
+    hi = nan_max(hi, pmax[(int64_t)b * D + d]);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, o, 64));
-    hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+    lo = nan_min(lo, __shfl_xor(lo, o, 64));
+    hi = nan_max(hi, __shfl_xor(hi, o, 64));
   }
   if (lane == 0) {
     slo[wave] = lo;
@@ -75,13 +92,13 @@ __global__ __launch_bounds__(256) void attr_finalize_kernel(const float* pmin, c
   }
   __syncthreads();
   if (t != 0) return;
-  lo = fminf(fminf(slo[0], slo[1]), fminf(slo[2], slo[3]));
-  hi = fmaxf(fmaxf(shi[0], shi[1]), fmaxf(shi[2], shi[3]));
+  lo = nan_min(nan_min(slo[0], slo[1]), nan_min(slo[2], slo[3]));
+  hi = nan_max(nan_max(shi[0], shi[1]), nan_max(shi[2], shi[3]));
   // float64 midpoint and half-range, rounded once
   const double mid = 0.5 * ((double)lo + (double)hi);
   const double half = 0.5 * ((double)hi - (double)lo);
   shift[d] = (float)mid;
-  scale[d] = half > 0.0 ? (float)half : 1.0f;
+  scale[d] = half > 0.0 || half != half ? (float)half : 1.0f;
 }
 
 // vals_t[d][i] = (vals[i][d] - shift[d]) / scale[d], through a 32 x 32 LDS
@@ -107,20 +124,37 @@ __global__ __launch_bounds__(256) void stage_values_kernel(const float* vals, in
   }
 }
 
+// vals_s[i][d] = (vals[i][d] - shift[d]) / scale[d], the input's layout.
+__global__ __launch_bounds__(256) void stage_rows_kernel(const float* vals, int64_t total, int D,
+                                                         const float* shift, const float* scale,
+                                                         float* vals_s) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * 256) {
+    const int d = (int)(e % D);
+    vals_s[e] = (float)(((double)vals[e] - (double)shift[d]) / (double)scale[d]);
+  }
+}
+
 }  // namespace
 
 int64_t stage_partial_blocks(int64_t n) { return (n + kRowsPerBlock - 1) / kRowsPerBlock; }
 
 hipError_t launch_stage(const float* vals, int64_t n, int D, float* pmin, float* pmax,
-                        float* shift, float* scale, float* vals_t, hipStream_t s) {
+                        float* shift, float* scale, float* vals_s, bool rows, hipStream_t s) {
   const int64_t nblk = stage_partial_blocks(n);
   const int dblk = (D + 31) / 32;
   hipLaunchKernelGGL(attr_range_kernel, dim3((unsigned)nblk, dblk), dim3(32, 8), 0, s, vals, n,
                      D, pmin, pmax);
   hipLaunchKernelGGL(attr_finalize_kernel, dim3(D), dim3(256), 0, s, pmin, pmax, (int)nblk, D,
                      shift, scale);
-  hipLaunchKernelGGL(stage_values_kernel, dim3((unsigned)((n + 31) / 32), dblk), dim3(32, 8), 0,
-                     s, vals, n, D, shift, scale, vals_t);
+  if (rows) {
+    const int64_t nb = (n * D + 255) / 256;
+    hipLaunchKernelGGL(stage_rows_kernel, dim3((unsigned)(nb < 65536 ? nb : 65536)), dim3(256), 0,
+                       s, vals, n * D, D, shift, scale, vals_s);
+  } else {
+    hipLaunchKernelGGL(stage_values_kernel, dim3((unsigned)((n + 31) / 32), dblk), dim3(32, 8),
+                       0, s, vals, n, D, shift, scale, vals_s);
+  }
   return hipGetLastError();
 }
 
