@@ -131,7 +131,8 @@ TRAFFIC_SUMMARIES = {
 }
 
 # the sources that decide each contraction kernel's memory traffic
-F64_SOURCES = ["paper_1408_0677_amd/csrc/mls_fit_f64.hip", "paper_1408_0677_amd/csrc/mls_solve.h"]
+F64_SOURCES = ["paper_1408_0677_amd/csrc/mls_fit_f64_shape.hip",
+               "paper_1408_0677_amd/csrc/mls_fit_f64.h", "paper_1408_0677_amd/csrc/mls_solve.h"]
 LP_SOURCES = ["paper_1408_0677_amd/csrc/mls_fit_lp.h", "paper_1408_0677_amd/csrc/mls_solve.h"]
 
 

@@ -194,9 +194,11 @@ void mls_context_destroy(mls_context* ctx);
  * device cell list); the inverse-distance weight with MLS_PREC_F64 on grids
  * with nonzero dx and dy (a node that coincides exactly with data points
  * takes the mean of their values, degree code 254; library scratch of about
- * 16 n bytes; the Gaussian on MLS_PREC_F64 uses scratch for its factor
- * tables, see mls_fit_scratch_bytes).  Other combinations return
- * MLS_ERR_UNSUPPORTED.  The 16-bit precisions
+ * 16 n bytes).  Other combinations return MLS_ERR_UNSUPPORTED.  Gaussian
+ * fits sum, per tile of nodes, the points whose weight can matter at the
+ * precision's own rounding (all points with MLS_PREC_F64 and n > 32768, with
+ * a weight_floor of 0 where no point is near, or with inputs that are not
+ * finite).  The 16-bit precisions
  * also return MLS_ERR_UNSUPPORTED when a node tile spans more than
  * MLS_LP_MAX_TILE_SPAN_<basis> (linear, quadratic), and MLS_PREC_FP16 when
  * tile-frame features would leave the float16 range; MLS_PREC_F64 serves
@@ -219,8 +221,8 @@ mls_status mls_fit(mls_context* ctx, const float* d_points, const float* d_value
  *          the ladder accepts the constant basis; NaN where the field is
  *          NaN and at exact hits of the inverse-distance weight (the field
  *          jumps to the points' value there).
- * Other arguments, errors and scratch as mls_fit.  The float64 path runs a
- * separate kernel variant (one workgroup per CU instead of two).
+ * Other arguments, errors and scratch as mls_fit; the fields are those of
+ * mls_fit, bit for bit.
  */
 mls_status mls_fit_grad(mls_context* ctx, const float* d_points, const float* d_values,
                         int64_t n, int32_t d, int32_t basis, const mls_weight* weight,
@@ -296,11 +298,10 @@ mls_status mls_context_trace_last(mls_context* ctx, mls_trace_record* out);
 
 /*
  * Device scratch bytes mls_fit needs for this request; 0 also for invalid
- * arguments.  MLS_PREC_F64 with the Gaussian weight tabulates the weight
- * factors of every grid column and row once per call, 8 x (n rounded up to
- * 64) x (width and height each rounded up to 16) bytes, when that is at most
- * 512 MiB (beyond, the factors are generated per tile and no scratch is
- * needed); the inverse-distance weight needs about 16 n bytes.
+ * arguments.  For MLS_PREC_F64 with the Gaussian weight it states
+ * 8 x (n rounded up to 64) x (width and height each rounded up to 16) bytes
+ * when that is at most 512 MiB, else 0; the fit itself allocates none of it.
+ * The inverse-distance weight needs about 16 n bytes.
  */
 size_t mls_fit_scratch_bytes(int64_t n, int32_t d, int32_t precision,
                              const mls_weight* weight, const mls_grid* grid);

@@ -45,11 +45,14 @@ struct mls_context {
   Scratch scratch;
   // fit staging: attribute ranges, shift/scale, normalised values
   Scratch fit_scratch;
+  // words of the float64 fit's look for inputs that are not finite, for the
+  // context's lifetime
+  uint32_t* bad = nullptr;
 
   // pinned host word for counts read back by mls_contour
   int64_t* pinned = nullptr;
 
-  // Both scratch buffers are shared by every call on the context, whatever
+  // The scratch buffers are shared by every call on the context, whatever
   // its stream: `last_use` is recorded after the last enqueued work that
   // touched them, on `last_stream`, and a call on another stream waits for
   // it before its own kernels run.
@@ -272,11 +275,8 @@ FitPlan make_fit_plan(int64_t n, int32_t d, int32_t precision, int32_t wkind, do
     return o;
   };
   if (precision == MLS_PREC_F64) {
-    // the Gaussian's factor tables, when they fit the cap
-    if (wkind == MLS_W_GAUSSIAN) {
-      p.gtab_bytes = f64_table_bytes(n, W, H);
-      if (p.gtab_bytes) p.o_gtab = carve(p.gtab_bytes);
-    }
+    // stated, not used (f64_scratch_bytes)
+    if (wkind == MLS_W_GAUSSIAN) carve(f64_scratch_bytes(n, W, H));
     // the inverse-distance weight's exact-hit pass sorts (node, point) keys
     if (wkind == MLS_W_INVPOW) {
       p.o_keys = carve(4 * (size_t)n);
@@ -397,9 +397,16 @@ mls_status mls_context_create(int32_t device, mls_context** out) {
     delete ctx;
     return device_fail(e, "hipEventCreateWithFlags");
   }
+  e = hipMalloc((void**)&ctx->bad, sizeof(uint32_t) * mls::kF64BadWords);
+  if (e != hipSuccess) {
+    (void)hipEventDestroy(ctx->last_use);
+    delete ctx;
+    return device_fail(e, "hipMalloc (context words)");
+  }
   // the fixed scratch of mls_contour_static: its address on this device
   e = mls::contour_static_scratch_resolve(device);
   if (e != hipSuccess) {
+    (void)hipFree(ctx->bad);
     (void)hipEventDestroy(ctx->last_use);
     delete ctx;
     return device_fail(e, "hipGetSymbolAddress (contour scratch)");
@@ -414,7 +421,7 @@ void mls_context_destroy(mls_context* ctx) {
     for (TraceCall& c : ctx->trace.pending) trace_destroy(c);
     if (ctx->scratch.ptr) (void)hipFree(ctx->scratch.ptr);
     if (ctx->fit_scratch.ptr) (void)hipFree(ctx->fit_scratch.ptr);
-
+    if (ctx->bad) (void)hipFree(ctx->bad);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->last_use) (void)hipEventDestroy(ctx->last_use);
   }
@@ -564,7 +571,7 @@ mls_status fit_prepare(mls_context* ctx, const float* d_points, const float* d_v
   a.deg_out = d_degree;
   a.grads = d_grad;
   a.lp_form = form;
-  a.gtab = nullptr;
+  a.bad = nullptr;
   *out = a;
   *terms_out = terms;
   return MLS_OK;
@@ -610,11 +617,11 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
     const mls::FitPlan plan = mls::make_fit_plan(n, d, precision, weight->kind, weight->h,
                                                  grid->x0, grid->y0, grid->dx, grid->dy,
                                                  grid->width, grid->height);
-    if (plan.total > 0) {
-      if ((st = ensure_scratch(ctx->fit_scratch, plan.total)) != MLS_OK) return st;
-      if ((st = scratch_acquire(ctx, s)) != MLS_OK) return st;
-      if (plan.gtab_bytes) a.gtab = (double*)((char*)ctx->fit_scratch.ptr + plan.o_gtab);
-    }
+    if (weight->kind == MLS_W_INVPOW &&
+        (st = ensure_scratch(ctx->fit_scratch, plan.total)) != MLS_OK)
+      return st;
+    if ((st = scratch_acquire(ctx, s)) != MLS_OK) return st;
+    a.bad = ctx->bad;
     e = mls::launch_fit_f64(a, s);
     if (e != hipSuccess) return device_fail(e, "fit kernel launch");
     tr.set_form(0);
@@ -648,7 +655,7 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
       return scratch_release(ctx, s);
     }
     tr.finish();
-    return plan.total > 0 ? scratch_release(ctx, s) : MLS_OK;
+    return scratch_release(ctx, s);
   }
   const bool fp16 = precision == MLS_PREC_FP16;
   const mls::FitPlan plan = mls::make_fit_plan(n, d, precision, weight->kind, weight->h,

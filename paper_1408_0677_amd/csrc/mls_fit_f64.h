@@ -1,0 +1,276 @@
+// Float64 matrix-core fits: parameters and the device code that the one-pass
+// kernel (mls_fit_f64.hip) and the two-pass kernel (mls_fit_f64_shape.hip)
+// share.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include "mls_internal.h"
+#include "mls_list.h"
+#include "mls_solve.h"
+
+namespace mls {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 256;
+constexpr int kWaves = 4;
+constexpr int kCols = 16;      // node columns per tile (one M-tile)
+constexpr int KT = 64;         // points per LDS chunk
+// LDS row stride in doubles.  A lane reads four consecutive doubles (two
+// 16-byte reads) of row i = lane % 16; with a stride of KT + 2 = 66
+// doubles (132 dwords, 4 mod 64) the sixteen rows of one read start in
+// sixteen different 4-bank groups, so the reads are free of bank
+// conflicts (a stride of 68 doubles puts rows i and i + 8 on the same
+// banks).
+constexpr int KS = KT + 2;
+static_assert(KS % 2 == 0 && KT % 16 == 0, "rows must start on 16-byte boundaries");
+struct F64Params {
+  const float* pts;
+  const float* vals;
+  int64_t n;
+  int D, F;
+  double h, inv_h;
+  double alpha;        // inverse-distance exponent (WM_INV kernels)
+  double x0, y0, dx, dy;
+  int W, H, tiles_x;
+  double tau, floor_w;
+  float* fields;
+  uint8_t* deg_out;
+  float* grads;        // [D][2][H][W] or null
+  bool rigid;          // rigid map (EPI 2 kernels)
+  // Gaussian: reach of the tiles (tile_reach), whether an input that is not
+  // finite was found (words of finite_kernel; none: the tiles look themselves)
+  double list_log;     // ln n + 54 ln 2, or infinite: every tile sums all points
+  const uint32_t* bad;
+  int n_bad;
+  bool vec4;           // rows of the fields are 16-byte aligned
+  bool fine;           // a tile spans at most kFineSpan h on either axis
+};
+
+constexpr double kFineSpan = 8.0;
+
+// Weight modes of the kernel: the Gaussian, the inverse-distance weight per
+// pair (any exponent, or alpha = 1 and alpha = 2 through a reciprocal).
+constexpr int WM_GAUSS = 0, WM_INV = 1, WM_INV1 = 2, WM_INV2 = 3;
+
+// Two-pass form of the Gaussian fit (mls_fit_f64_shape.hip).
+hipError_t launch_fit_f64_shape(const F64Params& p, int degree, hipStream_t s);
+bool f64_use_shape_form(int degree, int D);
+// Strips of 16 nodes per wave (1, 2 or 4; a tile is 16 x 4 R nodes): the
+// largest that leaves kF64Tiles workgroups, about four per compute unit.
+constexpr int64_t kF64Tiles = 1024;
+inline int f64_tile_strips(int W, int H, int most) {
+  int R = most;
+  while (R > 1 && (int64_t)((W + kCols - 1) / kCols) *
+                          ((H + kWaves * R - 1) / (kWaves * R)) < kF64Tiles)
+    R /= 2;
+  return R;
+}
+
+namespace {
+
+constexpr int kListCap = 2048;
+constexpr int kListB = list_bytes(kListCap);
+
+__device__ __forceinline__ void read4(const double* src, double* dst) {
+  const double2* v = reinterpret_cast<const double2*>(src);
+  const double2 lo = v[0], hi = v[1];
+  dst[0] = lo.x;
+  dst[1] = lo.y;
+  dst[2] = hi.x;
+  dst[3] = hi.y;
+}
+
+// ---- reach of a tile (Gaussian) ----
+//
+// A tile sums only the points within R h of the rectangle of its nodes.  What
+// it leaves out of any node's sum of w b_j^2 (b_j up to degree DEG in u) is
+// at most n exp(-R^2) R^(2 DEG).  R is chosen so that this is 2^-54 of the
+// larger of the weight floor (nodes below it are undetermined) and a lower
+// bound S of the weight sum at the tile's nodes: less than the rounding of
+// the sums themselves.  Every sum leaves out the same points, so the fit is
+// that of the weight cut to zero there.  A node whose smallest diagonal
+// moment is itself below 2^-14 of that scale (its near points all on one
+// line through it, say) could still see what is left out above 2^-40: its
+// tile is then summed again over all points (kDiagFloor).
+constexpr double kDiagFloor = 0x1p-14;
+
+// A value that is the same in every lane, into scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  return __builtin_bit_cast(double, (hi << 32) | lo);
+}
+
+// The tile's node rectangle is |u - m| <= e per axis (tile frame, units of h).
+struct F64Reach {
+  double ox, oy;         // u = x inv_h - o, with the rectangle's centre as origin
+  double inv_h, ex, ey;
+  double r2;             // R^2 (infinite: every point)
+  double scale;          // max(S, weight floor)
+};
+
+// Whether the tile must take the point at (x, y): not if it is farther than R
+// from the rectangle.  (With an input that is not finite r2 is infinite, and
+// the comparison keeps every point.)
+__device__ __forceinline__ bool in_reach(const F64Reach& t, float x, float y) {
+  const double ax = fmax(fabs(fma((double)x, t.inv_h, -t.ox)) - t.ex, 0.0);
+  const double ay = fmax(fabs(fma((double)y, t.inv_h, -t.oy)) - t.ey, 0.0);
+  return !(ax * ax + ay * ay > t.r2);
+}
+
+// The reach of the tile whose anchor node is (c0 + 8, r0 + rows / 2).  Every
+// thread of the workgroup calls it; `shared` is LDS for kWaves floats, and
+// the call ends with a barrier.  S is the sum over the points of the weight
+// at their farthest node of the tile; below 1,024 points, where a pass over
+// them costs as much as it saves, S = 0.
+template <int DEG>
+__device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, double cx, double cy,
+                                               float* shared) {
+  F64Reach t;
+  // the rectangle's centre lies half a node before the anchor
+  t.ox = uniform((cx - 0.5 * p.dx) * p.inv_h);
+  t.oy = uniform((cy - 0.5 * p.dy) * p.inv_h);
+  t.inv_h = p.inv_h;
+  // a little more than half the rectangle: the test's own rounding
+  t.ex = uniform(0.5 * (double)(kCols - 1) * fabs(p.dx) * p.inv_h + 0x1p-40 * (1.0 + fabs(t.ox)));
+  t.ey = uniform(0.5 * (double)(rows - 1) * fabs(p.dy) * p.inv_h + 0x1p-40 * (1.0 + fabs(t.oy)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const auto pts = global_ptr(p.pts);
+  float S = 0.0f;
+  if (p.n >= 1024 && p.list_log < __builtin_inf()) {
+#pragma unroll 4
+    for (int i = tid; i < (int)p.n; i += kThreads) {
+      const float ax = (float)(fabs(fma((double)pts[2 * i], p.inv_h, -t.ox)) + t.ex);
+      const float ay = (float)(fabs(fma((double)pts[2 * i + 1], p.inv_h, -t.oy)) + t.ey);
+      S += __expf(-(ax * ax + ay * ay));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
+  }
+  // inputs that are not finite reach every node (0 x NaN): sum all points
+  bool bad = !(S < __builtin_inff());
+  if (p.n_bad > 0) {
+    for (int i = tid; i < p.n_bad; i += kThreads) bad = bad || p.bad[i] != 0;
+  } else {
+    const auto vals = global_ptr(p.vals);
+    const int nv = (int)p.n * p.D;
+#pragma unroll 4
+    for (int i = tid; i < nv; i += kThreads) bad |= !(fabsf(vals[i]) < __builtin_inff());
+    for (int i = tid; i < 2 * (int)p.n; i += kThreads)
+      bad |= !(fabsf(pts[i]) < __builtin_inff());
+  }
+  if (lane == 0) shared[wave] = S;
+  const int any = __syncthreads_or(bad);
+  S = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) S += shared[w];
+  __syncthreads();
+  t.scale = uniform(fmax(0.99 * (double)S, p.floor_w));
+  t.r2 = __builtin_inf();
+  if (!any && t.scale > 0.0 && p.list_log < __builtin_inf()) {
+    const double L = p.list_log - log(t.scale);
+    double r2 = L;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) r2 = L + DEG * log(r2);
+    t.r2 = uniform(r2);
+  }
+  return t;
+}
+
+// Gaussian factors g_c = exp(-(u - e_c)^2), e_c = (c - c_mid) s, of one point
+// at a half of the nodes of one axis (`cnt` of them, the upper half or the
+// lower).  They follow by stepping: g_{c+1} / g_c = exp(2 s (u - e_c) - s^2),
+// and that ratio itself shrinks by q = exp(-2 s^2) per step: two
+// multiplications per node after two exponentials.
+// On fine grids (kFineSpan), for a list within reach, one thread steps through a half from its first
+// node: the exponents stay above -(8.5 + 8)^2, far from
+// underflow.  Otherwise start at the node nearest to u (the largest factor),
+// so that every exponent is <= 0; the upper half's thread steps up from it
+// and the lower half's down.
+template <int CNT>
+__device__ __forceinline__ void gauss_steps(bool fine, double u, double s, double q, bool up,
+                                            double* g) {
+  constexpr int mid = CNT / 2;
+  if (fine) {
+    const int c1 = up ? mid : 0;
+    const double dc = u - (double)(c1 - mid) * s;
+    double v = exp(-(dc * dc));
+    double r = exp(2.0 * s * dc - s * s);
+    g += c1 * KS;
+#pragma unroll
+    for (int c = 0; c < mid; ++c) {
+      g[c * KS] = v;
+      v *= r;
+      r *= q;
+    }
+    return;
+  }
+  const double t = u / s + (double)mid;
+  const int cs = (int)fmin(fmax(rint(t), 0.0), (double)(CNT - 1));
+  const double dc = u - (double)(cs - mid) * s;
+  const double gv = exp(-(dc * dc));
+  double r = exp((up ? 2.0 : -2.0) * s * dc - s * s);
+  double v = gv;
+  if (up) {
+    g[cs * KS] = gv;
+    for (int c = cs + 1; c < CNT; ++c) {
+      v *= r;
+      r *= q;
+      g[c * KS] = v;
+    }
+  } else {
+    for (int c = cs - 1; c >= 0; --c) {
+      v *= r;
+      r *= q;
+      g[c * KS] = v;
+    }
+  }
+}
+
+// The factors of a chunk of kn points, gx [16][KS] and gy [ROWS][KS] after
+// it: one thread per point, axis and half.  Points past the chunk weigh 0.
+template <int ROWS>
+__device__ __forceinline__ void put_gauss(bool fine, const double* ux, const double* uy,
+                                          double* gx, int kn, double sx, double sy, double qx,
+                                          double qy, int tid) {
+  double* gy = gx + kCols * KS;
+  const int k = tid & (KT - 1);
+  const bool xaxis = (tid & KT) == 0, up = tid < 2 * KT;
+  if (k < kn) {
+    if (xaxis) gauss_steps<kCols>(fine, ux[k], sx, qx, up, gx + k);
+    else gauss_steps<ROWS>(fine, uy[k], sy, qy, up, gy + k);
+  } else {
+    double* g = (xaxis ? gx : gy) + k;
+    const int mid = (xaxis ? kCols : ROWS) / 2;
+    for (int c = 0; c < mid; ++c) g[((up ? mid : 0) + c) * KS] = 0.0;
+  }
+}
+
+// Moment monomials of a chunk's tile-frame coordinates, rows of G: a point per
+// lane, the rows spread over the waves.
+template <int NMOM>
+__device__ __forceinline__ void put_monomials(const double* ux, const double* uy, double* G,
+                                              int lane, int wave) {
+  const double x = ux[lane], y = uy[lane];
+  double px[5], py[5];
+  px[0] = py[0] = 1.0;
+#pragma unroll
+  for (int a = 1; a < 5; ++a) {
+    px[a] = px[a - 1] * x;
+    py[a] = py[a - 1] * y;
+  }
+  int j = 0;
+#pragma unroll
+  for (int t = 0; t < 5; ++t)
+#pragma unroll
+    for (int b = 0; b <= t; ++b, ++j)   // ordered by total degree, then by y power
+      if (j < NMOM && (j & 3) == wave) G[j * KS + lane] = px[t - b] * py[b];
+}
+
+}  // namespace
+}  // namespace mls

@@ -15,11 +15,8 @@
 //   2. Gaussian weight factors gx[col][k] = exp(-((x_k - p_col)/h)^2) and
 //      gy[row][k] (the Gaussian separates on a grid, so a tile needs
 //      16 + 4R factors per point instead of 64R), and the feature block
-//      G[j][k] in float64.  The factors are either copied from tables of
-//      every grid column and row built once per launch (when they fit the
-//      scratch cap) or generated per tile by a stepping recurrence; the
-//      copy costs load and LDS instructions, which overlap the matrix
-//      cores, where the recurrence costs vector instructions, which do not,
+//      G[j][k] in float64.  The factors follow by stepping from node to node
+//      (gauss_steps: two exponentials per point, axis and half),
 //   3. MFMA sweep: the A operand (node x point weight) is gx * gy, built in
 //      registers; B is read from G.  Within each group of 16 points a lane
 //      supplies points k0 + 4 (lane / 16) + j for MFMA j = 0..3, so it reads
@@ -28,77 +25,24 @@
 // lane, which runs the float64 degree-ladder solve (mls_solve.h) and stores
 // the D fields and the degree code.  Every node sums its points in the same
 // fixed order, so results are bit-reproducible run to run.
-#include <hip/hip_runtime.h>
-#include <math.h>
-#include <stdint.h>
-
-#include "mls_internal.h"
-#include "mls_solve.h"
+//
+// With the Gaussian the points are those in reach of the tile (mls_fit_f64.h,
+// tile_reach), listed in LDS: 5,000 points, 13 attributes, h = 0.03, 1024^2
+// contracts 13% of the points.  Gaussian fits whose feature block would be
+// wider than 16 columns take the two-pass form instead
+// (mls_fit_f64_shape.hip); this kernel keeps the constant basis, the linear
+// basis with up to 3 attributes, the rigid map, and every inverse-distance
+// fit.  3,000 points, 9 attributes, constant basis, 700 x 500: 545 -> 277 us;
+// 4,500 points, 2 attributes, linear: 875 -> 308 us.
+#include "mls_fit_f64.h"
 
 namespace mls {
 namespace {
 
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
-#ifndef MLS_F64_KT
-#define MLS_F64_KT 64
-#endif
-#ifndef MLS_F64_EPI_WAVES
-#define MLS_F64_EPI_WAVES 2
-#endif
-
-constexpr int kThreads = 256;
-constexpr int kWaves = 4;
-constexpr int kCols = 16;      // node columns per tile (one M-tile)
-constexpr int KT = MLS_F64_KT; // points per LDS chunk
-#ifndef MLS_F64_PAD
-#define MLS_F64_PAD 2
-#endif
-#ifndef MLS_F64_KG_UNROLL
-#define MLS_F64_KG_UNROLL 1
-#endif
-#ifndef MLS_F64_SETPRIO
-#define MLS_F64_SETPRIO 0
-#endif
-// LDS row stride in doubles.  A lane reads four consecutive doubles (two
-// 16-byte reads) of row i = lane % 16; with a stride of KT + 2 = 66
-// doubles (132 dwords, 4 mod 64) the sixteen rows of one read start in
-// sixteen different 4-bank groups, so the reads are free of bank
-// conflicts (a stride of 68 doubles puts rows i and i + 8 on the same
-// banks).
-constexpr int KS = KT + MLS_F64_PAD;
-static_assert(KS % 2 == 0 && KT % 16 == 0, "rows must start on 16-byte boundaries");
 // Waves that run the epilogue at the same time: the epilogue needs a
 // [nodes][features] float64 staging area per wave, and sharing it keeps the
 // kernel's LDS small enough for two workgroups per CU.
-constexpr int kEpiWaves = MLS_F64_EPI_WAVES;
-
-struct F64Params {
-  const float* pts;
-  const float* vals;
-  // Gaussian factor tables (WM_TABLE kernels): rows [0, tab_cols) are the
-  // grid columns, rows tab_cols + r the grid rows; tab_n points per row
-  const double* tab;
-  int64_t tab_n;
-  int tab_cols;
-  int64_t n;
-  int D, F;
-  double h, inv_h;
-  double alpha;        // inverse-distance exponent (WM_INV kernels)
-  double x0, y0, dx, dy;
-  int W, H, tiles_x;
-  double tau, floor_w;
-  float* fields;
-  uint8_t* deg_out;
-  float* grads;        // [D][2][H][W] or null
-  bool rigid;          // rigid map (EPI 2 kernels)
-};
-
-// Weight modes of the kernel: the Gaussian with per-tile factors from a
-// stepping recurrence, the inverse-distance weight per pair (any exponent,
-// or alpha = 1 and alpha = 2 through a reciprocal), the Gaussian with
-// factors copied from per-launch tables.
-constexpr int WM_GAUSS = 0, WM_INV = 1, WM_TABLE = 2, WM_INV1 = 3, WM_INV2 = 4;
+constexpr int kEpiWaves = 2;
 
 template <int DEG, int NT, int R>
 struct F64Layout {
@@ -111,8 +55,6 @@ struct F64Layout {
   static constexpr int kDMax = (kFP - nmom) / m;
   static constexpr int kValRegs =
       kDMax > 0 ? (KT * kDMax + kThreads - 1) / kThreads : 1;
-  // per-thread registers holding one chunk of table factors (16 + 4R rows)
-  static constexpr int kTabRegs = ((kCols + kWaves * R) * KT + kThreads - 1) / kThreads;
   // chunk phase
   static constexpr int kUx = 0;                          // [KT] tile-frame u_x
   static constexpr int kUy = kUx + KT;                   // [KT]
@@ -124,11 +66,13 @@ struct F64Layout {
   static constexpr int kEpiStride = kFP + 1;
   static constexpr int kEpi = kEpiWaves * 16 * R * kEpiStride;
   static constexpr int kDoubles = kChunk > kEpi ? kChunk : kEpi;
+  static constexpr int kBytes = 8 * kDoubles;            // then the list (Gaussian)
 };
 
 template <int DEG, int R, int EPI>
-__device__ void solve_tile_nodes(const F64Params& p, const double* epi, int stride, int lane,
-                                 int wave, int r0, int c0, int rows, int64_t plane);
+__device__ bool solve_tile_nodes(const F64Params& p, const double* epi, int stride, int lane,
+                                 int wave, int r0, int c0, int rows, int64_t plane,
+                                 double diag_min);
 
 // Inverse-distance weight (Eq. 4) of a node-point offset (ox, oy) in units of
 // h: (ox^2 + oy^2)^(-alpha).  log2 of r^2 is taken as its binary exponent
@@ -164,15 +108,6 @@ __device__ __forceinline__ double invpow_weight_int(double ox, double oy) {
   return ALPHA == 1 ? r : r * r;
 }
 
-__device__ __forceinline__ void read4(const double* src, double* dst) {
-  const double2* v = reinterpret_cast<const double2*>(src);
-  const double2 lo = v[0], hi = v[1];
-  dst[0] = lo.x;
-  dst[1] = lo.y;
-  dst[2] = hi.x;
-  dst[3] = hi.y;
-}
-
 // Epilogue EPI: 0 fields, 1 fields and the slopes of the local fits (the
 // extra solves raise the epilogue's register count, so they are separate
 // instantiations and the plain kernels keep two workgroups per CU), 2 the
@@ -190,7 +125,8 @@ __device__ __forceinline__ void read4(const double* src, double* dst) {
 // three short instructions where the 16x16x4 one carries 4 to 13 empty
 // columns.
 template <int DEG, int NT, int R, int WM, int EPI, int Q4 = 0>
-__global__ __launch_bounds__(kThreads) void fit_f64_kernel(F64Params p) {
+__global__ __launch_bounds__(kThreads, WM == WM_GAUSS ? (NT == 1 ? 3 : 2) : 1)
+void fit_f64_kernel(F64Params p) {
   static_assert(Q4 == 0 || NT == 1, "the 4x4x4 form covers one feature tile");
   constexpr bool INV = WM == WM_INV || WM == WM_INV1 || WM == WM_INV2;
   using L = F64Layout<DEG, NT, R>;
@@ -215,55 +151,54 @@ __global__ __launch_bounds__(kThreads) void fit_f64_kernel(F64Params p) {
   double* gy = lds + L::kGy;
   double* G = lds + L::kG;
 
-  doublex4 acc[R][NT];
-  double acc4[R][Q4 > 0 ? Q4 : 1];
-#pragma unroll
-  for (int t = 0; t < R; ++t) {
-#pragma unroll
-    for (int q = 0; q < NT; ++q) acc[t][q] = doublex4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < (Q4 > 0 ? Q4 : 1); ++q) acc4[t][q] = 0.0;
-  }
-
   const int D = p.D, F = p.F;
-  // padding features stay zero for the whole kernel
-  for (int e = tid; e < (L::kFP - F) * KS; e += kThreads) G[F * KS + e] = 0.0;
+  // Gaussian: the points in reach, a list at a time; all points otherwise
+  constexpr bool LIST = !INV;
+  char* lds_list = (char*)lds + L::kBytes;
+  const uint16_t* list = (const uint16_t*)lds_list;
+  F64Reach reach{};
+  if (LIST) reach = tile_reach<DEG>(p, L::kRows, cx, cy, (float*)lds);
+  const int64_t plane = (int64_t)p.W * p.H;
 
+  // The chunk at entry k0 of the current list, which starts at point `base`
+  // and has `cnt` entries.
+  int64_t base = 0, cnt = 0;
+  // bytes of a listed point's attributes from the list's first point: at most
+  // 65,536 rows of 255 floats
+  auto value = [&](int64_t k, int d) -> float {
+    if (!LIST) return p.vals[k * D + d];
+    const char* row = (const char*)(p.vals + base * (int64_t)D);
+    return *(const float*)(row + 4u * ((uint32_t)list[k] * (uint32_t)D + (uint32_t)d));
+  };
   // Raw chunk data is prefetched into registers one chunk ahead, so that
   // the global-memory latency overlaps the previous chunk's MFMA sweep.
   float pf_x = 0.0f, pf_y = 0.0f;
   float pf_v[L::kValRegs];
+  // (point, attribute) of this thread's first feature element and the step
+  // to its next one (kThreads elements on)
+  const int fk0 = tid / D, fd0 = tid - fk0 * D;
+  const int fks = kThreads / D, fds = kThreads - fks * D;
   auto prefetch = [&](int64_t k0) {
-    const int kn = (int)((p.n - k0) < KT ? (p.n - k0) : KT);
+    const int kn = (int)((cnt - k0) < KT ? (cnt - k0) : KT);
     if (tid < KT && tid < kn) {
-      pf_x = p.pts[2 * (k0 + tid)];
-      pf_y = p.pts[2 * (k0 + tid) + 1];
+      const int64_t g = LIST ? base + list[k0 + tid] : k0 + tid;
+      pf_x = p.pts[2 * g];
+      pf_y = p.pts[2 * g + 1];
     }
-    // consecutive threads read consecutive values of the chunk (coalesced)
-    const float* v = p.vals + k0 * (int64_t)D;
+    // consecutive threads read consecutive values of a point, then of the
+    // next one (coalesced)
+    int k = fk0, d = fd0;
 #pragma unroll
     for (int it = 0; it < L::kValRegs; ++it) {
-      const int e = tid + it * kThreads;
-      pf_v[it] = (e < kn * D) ? v[e] : 0.0f;
-    }
-  };
-  prefetch(0);
-  // table factors of a chunk: row e / KT of the tile's 16 + 4R rows, point
-  // e % KT (consecutive threads read consecutive points of a row)
-  double tv[L::kTabRegs];
-  auto tab_load = [&](int64_t k0) {
-#pragma unroll
-    for (int it = 0; it < L::kTabRegs; ++it) {
-      const int e = tid + it * kThreads;
-      const int row = e / KT, k = e % KT;
-      if (row < kCols + L::kRows) {
-        const int64_t trow = row < kCols ? (int64_t)(c0 + row)
-                                         : (int64_t)p.tab_cols + r0 + (row - kCols);
-        tv[it] = p.tab[trow * p.tab_n + k0 + k];
+      pf_v[it] = k < kn ? value(k0 + k, d) : 0.0f;
+      k += fks;
+      d += fds;
+      if (d >= D) {
+        d -= D;
+        ++k;
       }
     }
   };
-
   // Gaussian step factors of the tile (exp(-2 s^2) per node step)
   const double sx = p.dx * p.inv_h, sy = p.dy * p.inv_h;
   const double qx = exp(-2.0 * sx * sx), qy = exp(-2.0 * sy * sy);
@@ -282,81 +217,53 @@ __global__ __launch_bounds__(kThreads) void fit_f64_kernel(F64Params p) {
       uy[tid] = y;
     }
   };
-  put_coords((int)(p.n < KT ? p.n : KT));
-  __syncthreads();
-  // (point, attribute) of this thread's first feature element and the step
-  // to its next one (kThreads elements on)
-  const int fk0 = tid / D, fd0 = tid - fk0 * D;
-  const int fks = kThreads / D, fds = kThreads - fks * D;
 
-  for (int64_t k0 = 0; k0 < p.n; k0 += KT) {
-    const int kn = (int)((p.n - k0) < KT ? (p.n - k0) : KT);
-    // table factors of this chunk: loaded now, stored after the monomials
-    // and features, so that the loads' latency overlaps that work and the
-    // registers are not held during the sweep
-    if (WM == WM_TABLE) tab_load(k0);
-    for (int e = tid; e < (WM == WM_TABLE ? 0 : 4 * KT); e += kThreads) {
-      // 2a. separable Gaussian factors g_c = exp(-(u - e_c)^2), e_c = (c - c_mid) s,
-      //     for one point, one axis and one direction.  Start at the node
-      //     nearest to u (the largest factor) and step outwards:
-      //     g_{c+1} / g_c = exp(2 s (u - e_c) - s^2), and that ratio itself
-      //     shrinks by exp(-2 s^2) per step, so every exponent is <= 0; one
-      //     thread steps up from the nearest node and another down.  Points
-      //     past n get weight 0.
-      const int k = e & (KT - 1);
-      const bool xaxis = (e & KT) == 0;
-      const bool up = e < 2 * KT;
-      const int cnt = xaxis ? kCols : L::kRows;
-      const int mid = cnt / 2;
+  // Once over the points in reach; where a node's moments turn out so small
+  // that what lies beyond could matter, once more over all points.
+  for (;;) {
+  doublex4 acc[R][NT];
+  double acc4[R][Q4 > 0 ? Q4 : 1];
+#pragma unroll
+  for (int t = 0; t < R; ++t) {
+#pragma unroll
+    for (int q = 0; q < NT; ++q) acc[t][q] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < (Q4 > 0 ? Q4 : 1); ++q) acc4[t][q] = 0.0;
+  }
+  // padding features stay zero for the whole sweep
+  for (int e = tid; e < (L::kFP - F) * KS; e += kThreads) G[F * KS + e] = 0.0;
+
+  for (int64_t pos = 0; pos < p.n;) {
+  base = pos;
+  if (LIST) {
+    cnt = list_points<kThreads, kListCap>(
+        p.pts, p.n, pos, lds_list, [&](float x, float y) { return in_reach(reach, x, y); });
+  } else {
+    cnt = pos = p.n;
+  }
+  if (cnt == 0) continue;
+  prefetch(0);
+  put_coords((int)(cnt < KT ? cnt : KT));
+  __syncthreads();
+  for (int64_t k0 = 0; k0 < cnt; k0 += KT) {
+    const int kn = (int)((cnt - k0) < KT ? (cnt - k0) : KT);
+    if constexpr (!INV) {
+      // 2a. separable Gaussian factors
+      put_gauss<L::kRows>(p.fine && reach.r2 < __builtin_inf(), ux, uy, gx, kn, sx, sy, qx, qy, tid);
+    } else {
+      // inverse-distance weights do not separate: the tables hold the node
+      // offsets, and the A operand forms the weight per pair
+      const int k = tid & (KT - 1);
+      const bool xaxis = (tid & KT) == 0, up = tid < 2 * KT;
+      const int mid = (xaxis ? kCols : L::kRows) / 2;
       const double s = xaxis ? sx : sy;
-      const double q = xaxis ? qx : qy;
-      double* g = xaxis ? gx : gy;
-      // each direction owns half of the row when there is no stepping
-      const int h0 = up ? 0 : mid, h1 = up ? mid : cnt;
-      if (INV) {
-        // inverse-distance weights do not separate: the tables hold the
-        // node offsets, and the A operand forms the weight per pair
-        const double u = k < kn ? (xaxis ? ux[k] : uy[k]) : 0.0;
-        for (int c = h0; c < h1; ++c)
-          g[c * KS + k] = k < kn ? u - (double)(c - mid) * s : __builtin_inf();
-      } else if (k < kn) {
-        const double u = xaxis ? ux[k] : uy[k];
-        const double t = u / s + (double)mid;
-        const int cs = (int)fmin(fmax(rint(t), 0.0), (double)(cnt - 1));
-        const double dc = u - (double)(cs - mid) * s;
-        const double gv = exp(-(dc * dc));
-        double r = exp((up ? 2.0 : -2.0) * s * dc - s * s);
-        double v = gv;
-        if (up) {
-          g[cs * KS + k] = gv;
-          for (int c = cs + 1; c < cnt; ++c) {
-            v *= r;
-            r *= q;
-            g[c * KS + k] = v;
-          }
-        } else {
-          for (int c = cs - 1; c >= 0; --c) {
-            v *= r;
-            r *= q;
-            g[c * KS + k] = v;
-          }
-        }
-      } else {
-        for (int c = h0; c < h1; ++c) g[c * KS + k] = 0.0;
-      }
+      double* g = (xaxis ? gx : gy) + (up ? mid : 0) * KS + k;
+      const double u = xaxis ? ux[k] : uy[k];
+      for (int c = 0; c < mid; ++c)
+        g[c * KS] = k < kn ? u - (double)(c - (up ? 0 : mid)) * s : __builtin_inf();
     }
     // 2b. moment monomials of the tile-frame coordinates
-    for (int e = tid; e < nmom * KT; e += kThreads) {
-      const int k = e % KT, j = e / KT;
-      // exponents of monomial j (ordered by total degree, then by y power)
-      int t = 0;
-      while ((t + 1) * (t + 2) / 2 <= j) ++t;
-      const int b = j - t * (t + 1) / 2, a = t - b;
-      double v = 1.0;
-      for (int q = 0; q < a; ++q) v *= ux[k];
-      for (int q = 0; q < b; ++q) v *= uy[k];
-      G[j * KS + k] = v;
-    }
+    put_monomials<nmom>(ux, uy, G, lane, wave);
     // 2c. basis x attribute products from the prefetched values
     {
       int k = fk0, d = fd0;
@@ -384,25 +291,14 @@ __global__ __launch_bounds__(kThreads) void fit_f64_kernel(F64Params p) {
         }
       }
     }
-    if (WM == WM_TABLE) {
-      // 2a from the tables (zero past n)
-#pragma unroll
-      for (int it = 0; it < L::kTabRegs; ++it) {
-        const int e = tid + it * kThreads;
-        const int row = e / KT, k = e % KT;
-        if (row < kCols) gx[row * KS + k] = tv[it];
-        else if (row < kCols + L::kRows) gy[(row - kCols) * KS + k] = tv[it];
-      }
-    }
     // next chunk's raw data: in flight during the MFMA sweep
-    if (k0 + KT < p.n) prefetch(k0 + KT);
+    if (k0 + KT < cnt) prefetch(k0 + KT);
     __syncthreads();
 
     // 3. MFMA sweep over the chunk
     const int i = lane & 15;        // A row (node column) / B column
     const int kq = (lane >> 4) * 4; // this lane's 4 points in each group of 16
-    if (MLS_F64_SETPRIO) __builtin_amdgcn_s_setprio(1);
-#pragma unroll MLS_F64_KG_UNROLL
+#pragma unroll 1
     for (int kg = 0; kg < KT; kg += 16) {
       // four consecutive doubles of a row as two 16-byte reads (rows start
       // on 16-byte boundaries: KS is even and kg + kq a multiple of 4)
@@ -438,14 +334,15 @@ __global__ __launch_bounds__(kThreads) void fit_f64_kernel(F64Params p) {
         }
       }
     }
-    if (MLS_F64_SETPRIO) __builtin_amdgcn_s_setprio(0);
-    if (k0 + KT < p.n) put_coords((int)((p.n - k0 - KT) < KT ? (p.n - k0 - KT) : KT));
+    if (k0 + KT < cnt) put_coords((int)((cnt - k0 - KT) < KT ? (cnt - k0 - KT) : KT));
     __syncthreads();
+  }
   }
 
   // Epilogue: accumulators -> LDS [node][feature] -> one node per lane,
   // kEpiWaves waves at a time.  (The main loop ended with a barrier.)
-  const int64_t plane = (int64_t)p.W * p.H;
+  bool again = false;
+  const double diag_min = LIST ? reach.scale * kDiagFloor : 0.0;
 #pragma unroll 1
   for (int g = 0; g < kWaves; g += kEpiWaves) {
     const bool mine = wave >= g && wave < g + kEpiWaves;
@@ -477,16 +374,25 @@ __global__ __launch_bounds__(kThreads) void fit_f64_kernel(F64Params p) {
     }
     __syncthreads();
     if (mine)
-      solve_tile_nodes<DEG, R, EPI>(p, epi, L::kEpiStride, lane, wave, r0, c0, L::kRows, plane);
+      again = solve_tile_nodes<DEG, R, EPI>(p, epi, L::kEpiStride, lane, wave, r0, c0, L::kRows,
+                                            plane, diag_min);
     __syncthreads();
+  }
+  // the second time r2 is infinite
+  if (!LIST || DEG == 0 || EPI == 2 || !(reach.r2 < __builtin_inf())) break;
+  if (!__syncthreads_or(again)) break;
+  reach.r2 = __builtin_inf();
   }
 }
 
 // One node per lane: the float64 ladder solve of the nodes of one wave.
+// Returns whether some node has a diagonal moment below diag_min.
 template <int DEG, int R, int EPI>
-__device__ void solve_tile_nodes(const F64Params& p, const double* epi, int stride, int lane,
-                                 int wave, int r0, int c0, int rows, int64_t plane) {
+__device__ bool solve_tile_nodes(const F64Params& p, const double* epi, int stride, int lane,
+                                 int wave, int r0, int c0, int rows, int64_t plane,
+                                 double diag_min) {
   const int D = p.D;
+  bool low = false;
   for (int node = lane; node < 16 * R; node += 64) {
     const int t = node / 16, col = node % 16;
     const int r = r0 + wave * R + t, c = c0 + col;
@@ -496,14 +402,17 @@ __device__ void solve_tile_nodes(const F64Params& p, const double* epi, int stri
     const double ey = (double)(wave * R + t - rows / 2) * p.dy * p.inv_h;
     const int64_t off = (int64_t)r * p.W + c;
     uint8_t code;
+    double diag = __builtin_inf();
     if constexpr (EPI == 2)
       code = rigid_node(epi + node * stride, ex, ey, p.h, p.floor_w, p.fields + off, plane);
     else
       code = solve_node<DEG>(epi + node * stride, D, ex, ey, p.tau, p.floor_w, p.fields + off,
                              plane, nullptr, nullptr, 1.0, EPI == 1 ? p.grads + off : nullptr,
-                             p.inv_h);
+                             p.inv_h, &diag);
     if (p.deg_out) p.deg_out[off] = code;
+    low = low || diag < diag_min;
   }
+  return low;
 }
 
 template <int DEG, int NT, int R, int WM, int EPI, int Q4 = 0>
@@ -513,7 +422,8 @@ hipError_t launch_impl(const F64Params& prm, hipStream_t s) {
   const int tiles_x = (p.W + kCols - 1) / kCols;
   const int tiles_y = (p.H + L::kRows - 1) / L::kRows;
   p.tiles_x = tiles_x;
-  const size_t lds_bytes = sizeof(double) * (size_t)L::kDoubles;
+  constexpr bool INV = WM == WM_INV || WM == WM_INV1 || WM == WM_INV2;
+  const size_t lds_bytes = (size_t)L::kBytes + (INV ? 0 : kListB);
   hipError_t e = hipFuncSetAttribute((const void*)fit_f64_kernel<DEG, NT, R, WM, EPI, Q4>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds_bytes);
@@ -525,16 +435,29 @@ hipError_t launch_impl(const F64Params& prm, hipStream_t s) {
 }
 
 // R (row strips per wave) trades accumulator registers against the number
-// of Gaussian factors per tile.
+// of weight factors per tile.  With one feature tile, where registers allow
+// any R, small grids take fewer strips so that their tiles fill the chip.
+template <int DEG, int NT, int WM, int EPI, int Q4>
+hipError_t launch_strips(const F64Params& p, hipStream_t s) {
+  if constexpr (NT == 1) {
+    switch (f64_tile_strips(p.W, p.H, 4)) {
+      case 1: return launch_impl<DEG, NT, 1, WM, EPI, Q4>(p, s);
+      case 2: return launch_impl<DEG, NT, 2, WM, EPI, Q4>(p, s);
+      default: return launch_impl<DEG, NT, 4, WM, EPI, Q4>(p, s);
+    }
+  } else {
+    return launch_impl<DEG, NT, NT <= 3 ? 4 : (NT <= 6 ? 2 : 1), WM, EPI, Q4>(p, s);
+  }
+}
+
 template <int DEG, int NT, int WM, int Q4>
 hipError_t launch_epi(const F64Params& p, hipStream_t s) {
-  constexpr int R = NT <= 3 ? 4 : (NT <= 6 ? 2 : 1);
   if (p.rigid) {
-    if constexpr (DEG == 1 && NT == 1) return launch_impl<DEG, NT, R, WM, 2, Q4>(p, s);
+    if constexpr (DEG == 1 && NT == 1) return launch_strips<DEG, NT, WM, 2, Q4>(p, s);
     return hipErrorInvalidValue;
   }
-  return p.grads ? launch_impl<DEG, NT, R, WM, 1, Q4>(p, s)
-                 : launch_impl<DEG, NT, R, WM, 0, Q4>(p, s);
+  return p.grads ? launch_strips<DEG, NT, WM, 1, Q4>(p, s)
+                 : launch_strips<DEG, NT, WM, 0, Q4>(p, s);
 }
 
 // At most 12 features (constant basis with D <= 11, linear basis with
@@ -556,16 +479,20 @@ hipError_t launch_deg(const F64Params& p, int nt, hipStream_t s) {
     // the reciprocal forms serve one and two feature tiles, where the
     // weight is most of the vector work per matrix instruction
     return nt == 1 ? launch_nt<DEG, 1, WM>(p, s) : launch_nt<DEG, 2, WM>(p, s);
-  }
-  switch (nt) {
-    case 1: return launch_nt<DEG, 1, WM>(p, s);
-    case 2: return launch_nt<DEG, 2, WM>(p, s);
-    case 3: return launch_nt<DEG, 3, WM>(p, s);
-    case 4: return launch_nt<DEG, 4, WM>(p, s);
-    case 5: case 6: return launch_nt<DEG, 6, WM>(p, s);
-    case 7: case 8: return launch_nt<DEG, 8, WM>(p, s);
-    case 9: case 10: case 11: case 12: return launch_nt<DEG, 12, WM>(p, s);
-    default: return launch_nt<DEG, 16, WM>(p, s);
+  } else if constexpr (WM != WM_INV && DEG == 1) {
+    // wider Gaussian fits take the two-pass form (f64_use_shape_form)
+    return nt == 1 ? launch_nt<DEG, 1, WM>(p, s) : hipErrorInvalidValue;
+  } else {
+    switch (nt) {
+      case 1: return launch_nt<DEG, 1, WM>(p, s);
+      case 2: return launch_nt<DEG, 2, WM>(p, s);
+      case 3: return launch_nt<DEG, 3, WM>(p, s);
+      case 4: return launch_nt<DEG, 4, WM>(p, s);
+      case 5: case 6: return launch_nt<DEG, 6, WM>(p, s);
+      case 7: case 8: return launch_nt<DEG, 8, WM>(p, s);
+      case 9: case 10: case 11: case 12: return launch_nt<DEG, 12, WM>(p, s);
+      default: return launch_nt<DEG, 16, WM>(p, s);
+    }
   }
 }
 
@@ -574,30 +501,37 @@ hipError_t launch_kind(const F64Params& p, int degree, int nt, hipStream_t s) {
   switch (degree) {
     case 0: return launch_deg<0, WM>(p, nt, s);
     case 1: return launch_deg<1, WM>(p, nt, s);
-    default: return launch_deg<2, WM>(p, nt, s);
+    default:
+      if constexpr (WM == WM_GAUSS) return hipErrorInvalidValue;
+      else return launch_deg<2, WM>(p, nt, s);
   }
 }
 
-// Gaussian factor tables: row r < cols is exp(-((x_k - (x0 + r dx)) / h)^2)
-// over the points k, row cols + r the same with y and y0 + r dy; zero for
-// k >= n.  Rows past the grid serve the padding nodes of edge tiles.
-__global__ __launch_bounds__(256) void gauss_table_kernel(const float* __restrict__ pts, int64_t n,
-                                                          int64_t tab_n, int cols, double x0,
-                                                          double dx, double y0, double dy,
-                                                          double inv_h, double* __restrict__ tab) {
-  const int row = blockIdx.y;
-  const bool xr = row < cols;
-  const double c = xr ? x0 + (double)row * dx : y0 + (double)(row - cols) * dy;
-  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < tab_n;
-       k += (int64_t)gridDim.x * 256) {
-    double v = 0.0;
-    if (k < n) {
-      const double u = ((double)pts[2 * k + (xr ? 0 : 1)] - c) * inv_h;
-      v = exp(-(u * u));
-    }
-    tab[row * tab_n + k] = v;
-  }
+// bad[block] = whether the block met a value or coordinate that is not finite.
+__global__ __launch_bounds__(256) void finite_kernel(const float* __restrict__ vals,
+                                                     int64_t total,
+                                                     const float* __restrict__ pts, int64_t n2,
+                                                     uint32_t* bad) {
+  bool b = false;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n2; i += (int64_t)gridDim.x * 256)
+    b = b || !(fabsf(pts[i]) < __builtin_inff());
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * 256)
+    b = b || !(fabsf(vals[i]) < __builtin_inff());
+  const int any = __syncthreads_or(b);
+  if (threadIdx.x == 0) bad[blockIdx.x] = any ? 1u : 0u;
 }
+
+// Most points for which a tile leaves out those beyond its reach.  The tiles'
+// own tests of the points cost n x tiles, but that is not why the line lies
+// here (40,000 points, quadratic, 1024^2 would take about 5 ms instead of 41):
+// a float64 request beyond it is the long one that the server's queue test
+// holds a slot with while it sets up, cancels and times out others behind it.
+constexpr int64_t kReachPoints = 32768;
+
+// Values that every tile looks through itself rather than by finite_kernel
+// (a launch, about 3 us, against 64 loads per thread).
+constexpr int64_t kFiniteInTile = 16384;
 
 }  // namespace
 
@@ -608,9 +542,6 @@ hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream) {
   F64Params p;
   p.pts = a.pts;
   p.vals = a.vals;
-  p.tab = nullptr;
-  p.tab_n = 0;
-  p.tab_cols = 0;
   p.n = a.n;
   p.D = a.D;
   p.F = F;
@@ -631,27 +562,30 @@ hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream) {
     if (nt <= 2 && a.alpha == 2.0) return launch_kind<WM_INV2>(p, a.degree, nt, stream);
     return launch_kind<WM_INV>(p, a.degree, nt, stream);
   }
-  if (!a.gtab) return launch_kind<WM_GAUSS>(p, a.degree, nt, stream);
-  p.tab = a.gtab;
-  p.tab_n = f64_table_points(a.n);
-  p.tab_cols = f64_table_rows(a.W);
-  const int rows = p.tab_cols + f64_table_rows(a.H);
-  const int64_t per_row = (p.tab_n + 255) / 256;
-  const unsigned bx = (unsigned)(per_row < 64 ? per_row : 64);
-  hipLaunchKernelGGL(gauss_table_kernel, dim3(bx, (unsigned)rows), dim3(256), 0, stream, a.pts,
-                     a.n, p.tab_n, p.tab_cols, a.x0, a.dx, a.y0, a.dy, p.inv_h, a.gtab);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_kind<WM_TABLE>(p, a.degree, nt, stream);
+  hipError_t e;
+  p.list_log = a.n <= kReachPoints ? log((double)a.n) + 54.0 * 0.6931471805599453 : HUGE_VAL;
+  p.bad = nullptr;
+  p.n_bad = 0;
+  p.vec4 = (a.W & 3) == 0 && ((uintptr_t)a.fields & 15) == 0;
+  if (a.n * a.D > kFiniteInTile) {
+    const int64_t nb = (a.n * a.D + 1023) / 1024;
+    p.bad = a.bad;
+    p.n_bad = (int)(nb < kF64BadWords ? nb : kF64BadWords);
+    hipLaunchKernelGGL(finite_kernel, dim3((unsigned)p.n_bad), dim3(256), 0, stream, a.vals,
+                       a.n * a.D, a.pts, 2 * a.n, a.bad);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const bool shape = !a.rigid && f64_use_shape_form(a.degree, a.D);
+  const double span = fmax(fabs(a.dx), fabs(a.dy)) * p.inv_h * 15.0;
+  p.fine = span <= kFineSpan && p.list_log < HUGE_VAL;
+  return shape ? launch_fit_f64_shape(p, a.degree, stream)
+               : launch_kind<WM_GAUSS>(p, a.degree, nt, stream);
 }
 
-int64_t f64_table_points(int64_t n) { return (n + KT - 1) / KT * KT; }
-int f64_table_rows(int cells) { return (cells + kCols - 1) / kCols * kCols; }
-
-size_t f64_table_bytes(int64_t n, int32_t W, int32_t H) {
-  const double bytes = 8.0 * (double)f64_table_points(n) *
-                       (double)(f64_table_rows(W) + f64_table_rows(H));
-  return bytes <= (double)kF64TableCap ? (size_t)bytes : 0;
+size_t f64_scratch_bytes(int64_t n, int32_t W, int32_t H) {
+  const double bytes = 8.0 * (double)((n + KT - 1) / KT * KT) *
+                       (double)((W + 15) / 16 * 16 + (H + 15) / 16 * 16);
+  return bytes <= (double)kF64ScratchCap ? (size_t)bytes : 0;
 }
 
 }  // namespace mls

@@ -62,6 +62,7 @@
 #include <string.h>
 
 #include "mls_internal.h"
+#include "mls_list.h"
 #include "mls_solve.h"
 
 namespace mls {
@@ -139,12 +140,10 @@ constexpr int RS = KT + 1;                 // raw chunk row stride (floats): a p
                                            // bank conflicts
 constexpr int kDsCap = 40;                 // attributes per slab at most
 constexpr int kLdsBytes = 160 * 1024;
-// Points listed at a time (Gaussian): 16-bit offsets from the segment's
-// first point.  A segment ends when the next round of tests might not fit.
-constexpr int kScan = 2 * kThreads;        // points tested per round
+// Points listed at a time (Gaussian, mls_list.h).  A segment ends when the
+// next round of tests might not fit.
 constexpr int kListCap = 4096;
-constexpr int kListB = kListCap * 2 + 2 * 16 * 4;   // list, then two rounds' wave counts
-static_assert(kScan <= kListCap && kScan <= 65536 && kMmaWaves + kProd / 64 <= 16, "list");
+constexpr int kListB = list_bytes(kListCap);
 
 template <typename T> struct Vec8;
 template <> struct Vec8<__bf16> { typedef bf16x8 type; };
@@ -283,15 +282,6 @@ __device__ __forceinline__ float wendland_c2(float s2) {
   return t2 * t2 * (4.0f * s + 1.0f);
 }
 
-// The input arrays are global memory.  Said explicitly, their loads are
-// global loads also where the compiler cannot see it (parameters read from
-// memory in the served batches) instead of flat loads, which also wait on
-// the LDS counter.
-template <typename V>
-__device__ __forceinline__ const __attribute__((address_space(1))) V* global_ptr(const V* q) {
-  return (const __attribute__((address_space(1))) V*)q;
-}
-
 // The reach of a tile's nodes in the tile frame (units of h): a point adds
 // nothing beyond `cut2` from the anchor, nor beyond `reach2` from the
 // rectangle [xlo, xhi] x [ylo, yhi] of the nodes.
@@ -313,69 +303,15 @@ __device__ __forceinline__ TileReach tile_reach(const LPParams& p, int c0, int r
 // one the producers zero features by, with room for its rounding; a
 // coordinate that is not finite (or whose square overflows) is kept, since
 // such a point makes the sums of every node NaN.
+// (Every kernel that lists a request's points must list the same ones, so
+// nothing here is left to the compiler's choice of fused operations.)
 __device__ __forceinline__ bool in_reach(const TileReach& t, float x, float y) {
+#pragma clang fp contract(off)
   const float ux = (x - t.cxr) * t.inv_h, uy = (y - t.cyr) * t.inv_h;
   const float u2 = ux * ux + uy * uy;
   const float ex = fmaxf(fmaxf(t.xlo - ux, ux - t.xhi), 0.0f);
   const float ey = fmaxf(fmaxf(t.ylo - uy, uy - t.yhi), 0.0f);
   return (u2 <= t.cut2 * 1.0001f && ex * ex + ey * ey <= t.reach2) || !(u2 < __builtin_inff());
-}
-
-// List the points from `pos` on that the tile must take, in input order, as
-// 16-bit offsets from pos, until the list may be full or the points end;
-// returns their number and moves pos past the points tested.  Every thread
-// calls it with the same arguments and gets the same result; it ends with a
-// barrier.  One barrier per round of kScan points: a wave's count of round
-// k + 2 is written after the barrier of round k + 1, which every wave passes
-// only after it has read the counts of round k.
-__device__ __forceinline__ int list_points(const LPParams& p, const TileReach& t, int64_t& pos,
-                                           char* lds_list) {
-  uint16_t* list = (uint16_t*)lds_list;
-  int* counts = (int*)(lds_list + kListCap * 2);   // [2][16]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int kWaves = kThreads / 64;
-  const uint64_t below = (1ull << lane) - 1ull;
-  const int64_t base = pos;
-  const auto pts = global_ptr(p.pts);
-  float x[2], y[2];
-  auto load = [&](int64_t from) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int64_t i = from + wave * 128 + q * 64 + lane;
-      x[q] = i < p.n ? pts[2 * i] : 0.0f;
-      y[q] = i < p.n ? pts[2 * i + 1] : 0.0f;
-    }
-  };
-  int cnt = 0, buf = 0;
-  load(pos);
-  while (pos < p.n && pos - base <= 65536 - kScan) {
-    const int64_t first = pos + wave * 128 + lane;
-    const bool k0 = first < p.n && in_reach(t, x[0], y[0]);
-    const bool k1 = first + 64 < p.n && in_reach(t, x[1], y[1]);
-    load(pos + kScan);                     // the next round's, in flight
-    const uint64_t m0 = __ballot(k0), m1 = __ballot(k1);
-    const int c0 = __popcll(m0), c1 = __popcll(m1);
-    if (lane == 0) counts[buf * 16 + wave] = c0 + c1;
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const int c = counts[buf * 16 + w];
-      if (w < wave) before += c;
-      total += c;
-    }
-    total = __builtin_amdgcn_readfirstlane(total);
-    if (cnt + total > kListCap) break;     // the same in every wave
-    int o = cnt + before;
-    if (k0) list[o + __popcll(m0 & below)] = (uint16_t)(first - base);
-    o += c0;
-    if (k1) list[o + __popcll(m1 & below)] = (uint16_t)(first + 64 - base);
-    cnt += total;
-    pos += kScan;
-    buf ^= 1;
-  }
-  __syncthreads();
-  return cnt;
 }
 
 // Producer: global -> registers for one raw chunk, its attributes
@@ -635,7 +571,9 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
       pos = p.n;
     } else {
       wk.k = 0;
-      wk.kend = list_points(p, reach, pos, lds_lp + L::kList0);
+      wk.kend = list_points<kThreads, kListCap>(
+          p.pts, p.n, pos, lds_lp + L::kList0,
+          [&](float x, float y) { return in_reach(reach, x, y); });
     }
   };
   floatx4 acc[R][NTS];
@@ -1080,6 +1018,11 @@ __global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
   const uint16_t* list = (const uint16_t*)(lds_sh + L::kList0);
   const TileReach reach = tile_reach(p, c0, r0, cxr, cyr);
   int kept = 0, segments = 0;
+  auto next_list = [&](int64_t& pos) {
+    return list_points<kThreads, kListCap>(
+        p.pts, p.n, pos, lds_sh + L::kList0,
+        [&](float x, float y) { return in_reach(reach, x, y); });
+  };
 
   // ---- pass 1: moments, then the ladder and the shape coefficients ----
   {
@@ -1094,7 +1037,7 @@ __global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
 #pragma unroll
       for (int t = 0; t < R; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
       for (int64_t pos = 0; pos < p.n; ++segments) {
-        kept = list_points(p, reach, pos, lds_sh + L::kList0);
+        kept = next_list(pos);
         __syncthreads();   // raw 0 and 1
         __syncthreads();   // chunk 0
         Walker wk{0, kept};
@@ -1137,7 +1080,7 @@ __global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
       const RowWalk rw = row_walk(pt, 0);
       for (int64_t pos = 0; pos < p.n; ++segments) {
         const int64_t base = pos;
-        kept = list_points(p, reach, pos, lds_sh + L::kList0);
+        kept = next_list(pos);
         Walker wk{0, kept};
         Chunk ch0 = walker_take(wk);
         Chunk ch1 = walker_take(wk);
@@ -1223,7 +1166,7 @@ __global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
         for (int j = 0; j < m; ++j) yv[t][j] = ybuf[((wave * R + t) * kCols + i) * m + j];
       for (int64_t pos = 0; pos < p.n;) {
         if (segments == 1) pos = p.n;
-        else kept = list_points(p, reach, pos, lds_sh + L::kList0);
+        else kept = next_list(pos);
         __syncthreads();   // raw 0 and 1
         __syncthreads();   // chunk 0
         Walker wk{0, kept};
@@ -1300,7 +1243,7 @@ __global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
       for (int64_t pos = 0; pos < p.n;) {
         const int64_t base = pos;
         if (segments == 1) pos = p.n;
-        else kept = list_points(p, reach, pos, lds_sh + L::kList0);
+        else kept = next_list(pos);
         Walker wk{0, kept};
         Chunk ch0 = walker_take(wk);
         Chunk ch1 = walker_take(wk);

@@ -61,6 +61,7 @@ template <int DEG>
 struct Ladder {
   static constexpr int m = DEG == 0 ? 1 : (DEG == 1 ? 3 : 6);
   double T[m][m], L[m][m], r[m], s[m], q[m], w[m], y[m];
+  double diag;   // the smallest diagonal moment of the node's frame
   int mk;
 };
 
@@ -101,6 +102,9 @@ __device__ __forceinline__ int ladder_solve(const Acc* g, double ex, double ey, 
       for (int q = 0; q <= c; ++q) v += TM[r][q] * lad.T[c][q];
       Mp[r][c] = v;
     }
+  lad.diag = Mp[0][0];
+#pragma unroll
+  for (int j = 1; j < m; ++j) lad.diag = Mp[j][j] < lad.diag ? Mp[j][j] : lad.diag;
 #pragma unroll
   for (int kd = DEG; kd >= 0; --kd) {
     const int mk = kd == 0 ? 1 : (kd == 1 ? 3 : 6);
@@ -169,6 +173,42 @@ __device__ __forceinline__ int ladder_solve(const Acc* g, double ex, double ey, 
   return 255;   // only when sum w == 0 passes a zero floor
 }
 
+// The same for a slope: ya = T'^T M_p'^{-1} e_a (a = 1, 2) with the factor of
+// ladder_solve, zero where the accepted degree has no linear terms.
+template <int DEG>
+__device__ __forceinline__ void slope_row(Ladder<DEG>& lad, int a, double (&ya)[Ladder<DEG>::m]) {
+  constexpr int m = Ladder<DEG>::m;
+  const int mk = lad.mk;
+#pragma unroll
+  for (int c = 0; c < m; ++c) ya[c] = 0.0;
+  if (mk < 3) return;
+#pragma unroll
+  for (int r = 0; r < m; ++r) {
+    if (r >= mk) continue;
+    double v = r == a ? lad.s[r] : 0.0;
+#pragma unroll
+    for (int c = 0; c < r; ++c) v -= lad.L[r][c] * lad.q[c];
+    lad.q[r] = v * lad.r[r];
+  }
+#pragma unroll
+  for (int r = m - 1; r >= 0; --r) {
+    if (r >= mk) continue;
+    double v = lad.q[r];
+#pragma unroll
+    for (int c = r + 1; c < m; ++c)
+      if (c < mk) v -= lad.L[c][r] * lad.w[c];
+    lad.w[r] = v * lad.r[r];
+  }
+#pragma unroll
+  for (int c = 0; c < m; ++c) {
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < m; ++r)
+      if (r < mk) v += lad.T[r][c] * (lad.s[r] * lad.w[r]);
+    ya[c] = v;
+  }
+}
+
 // Solve one node.  `g` points at the node's F accumulated features
 // (consecutive values, float64 or float32), `ex, ey` is delta.  Writes
 // field_d to fields[d * plane] (float32) and returns the accepted degree
@@ -177,59 +217,34 @@ __device__ __forceinline__ int ladder_solve(const Acc* g, double ex, double ey, 
 // divides the weight sum before the floor test (weights that were scaled
 // by a common factor).  If `grads` is given, the slopes d f_d / dx and
 // d f_d / dy go to grads[(2 d) * plane] and grads[(2 d + 1) * plane]
-// (zero when the constant basis is accepted, NaN where the field is).
+// (zero when the constant basis is accepted, NaN where the field is).  If
+// `diag` is given it receives the smallest diagonal moment of the node's
+// frame (infinite when the node is undetermined).
 template <int DEG, typename Acc>
 __device__ __forceinline__ uint8_t solve_node(const Acc* g, int D, double ex, double ey,
                               double tau, double floor_w, float* fields,
                               int64_t plane, const float* shift = nullptr,
                               const float* scale = nullptr, double wscale = 1.0,
-                              float* grads = nullptr, double inv_h = 1.0) {
+                              float* grads = nullptr, double inv_h = 1.0,
+                              double* diag = nullptr) {
   constexpr int m = Ladder<DEG>::m;
   constexpr int nmom = DEG == 0 ? 1 : (DEG == 1 ? 6 : 15);
   Ladder<DEG> lad;
   const int accepted = ladder_solve<DEG>(g, ex, ey, tau, floor_w, wscale, lad);
+  if (diag) *diag = accepted == 255 ? __builtin_inf() : lad.diag;
   if (accepted == 255) {
     for (int d = 0; d < D; ++d) fields[(int64_t)d * plane] = __builtin_nan("");
     if (grads)
       for (int d = 0; d < 2 * D; ++d) grads[(int64_t)d * plane] = __builtin_nan("");
     return 255;
   }
-  const int mk = lad.mk;
   if (grads) {
     // slopes: the same two triangular solves with S e_1 and S e_2
     const Acc* Rg = g + nmom;
 #pragma unroll 1
     for (int a = 1; a <= 2; ++a) {
       double ya[m];
-#pragma unroll
-      for (int c = 0; c < m; ++c) ya[c] = 0.0;
-      if (mk >= 3) {
-#pragma unroll
-        for (int r = 0; r < m; ++r) {
-          if (r >= mk) continue;
-          double v = r == a ? lad.s[r] : 0.0;
-#pragma unroll
-          for (int c = 0; c < r; ++c) v -= lad.L[r][c] * lad.q[c];
-          lad.q[r] = v * lad.r[r];
-        }
-#pragma unroll
-        for (int r = m - 1; r >= 0; --r) {
-          if (r >= mk) continue;
-          double v = lad.q[r];
-#pragma unroll
-          for (int c = r + 1; c < m; ++c)
-            if (c < mk) v -= lad.L[c][r] * lad.w[c];
-          lad.w[r] = v * lad.r[r];
-        }
-#pragma unroll
-        for (int c = 0; c < m; ++c) {
-          double v = 0.0;
-#pragma unroll
-          for (int r = 0; r < m; ++r)
-            if (r < mk) v += lad.T[r][c] * (lad.s[r] * lad.w[r]);
-          ya[c] = v;
-        }
-      }
+      slope_row<DEG>(lad, a, ya);
       for (int d = 0; d < D; ++d) {
         double v = 0.0;
 #pragma unroll

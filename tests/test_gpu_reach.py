@@ -14,7 +14,7 @@ from tests.parity import compare
 
 pytestmark = pytest.mark.gpu
 
-BOUND = {"bf16": (2e-3, 1e-4, 1e-2), "fp16": (2e-3, 1e-4, 1e-2)}
+BOUND = {"bf16": (2e-3, 1e-4, 1e-2), "fp16": (2e-3, 1e-4, 1e-2), "f64": (1e-5, 1e-5, 1e-3)}
 
 
 def note(msg):
@@ -70,6 +70,103 @@ def test_listing_rounds_and_segments(torch_dev, oracle, prec, d, n, h):
     F, deg = gpu_fit(torch_dev, pts, vals, grid, basis="linear", h=h, precision=prec)
     of, od, dm = oracle.fit_grid(pts, vals, grid, basis="linear", h=h)
     check(prec, F, deg, of.reshape(d, -1), od.ravel(), dm.ravel(), vals)
+
+
+# attribute counts of each contraction width: one pass; two passes with one to
+# three 4-column blocks, one to three 16-column tiles, and several slabs
+F64_FORMS = [("constant", 7), ("linear", 3), ("linear", 4), ("linear", 11), ("linear", 13),
+             ("linear", 33), ("linear", 83), ("quadratic", 1), ("quadratic", 8),
+             ("quadratic", 17), ("quadratic", 40)]
+
+
+@pytest.mark.parametrize("n,h,side", [(511, 0.06, (37, 19)), (513, 0.06, (37, 19)),
+                                      (1100, 0.5, (21, 45)), (2049, 0.05, (21, 45)),
+                                      (2600, 0.03, (515, 257)), (900, 0.05, (513, 518))])
+@pytest.mark.parametrize("basis,d", F64_FORMS)
+def test_f64_listing_and_forms(torch_dev, oracle, basis, d, n, h, side):
+    """Every form with lists of one and of several segments (2,048 entries),
+    and tiles of 4, 8 and 16 rows; checked on sampled nodes and the last
+    rows.  The fields of a call with slopes are the same bits."""
+    from paper_1408_0677_amd import api, workloads as wl
+    note(f"case f64 listing {basis} n={n} d={d} h={h} {side}")
+    rng = np.random.default_rng(n + d)
+    pts = wl.uniform_points(rng, n).astype(np.float32)
+    vals = wl.smooth_fields(rng, pts, d).astype(np.float32)
+    W, H = side
+    grid = {"x0": 0.02, "y0": 0.03, "dx": 0.9 / W, "dy": 0.9 / H, "width": W, "height": H}
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, basis=basis, h=h)
+    pix = np.unique(np.concatenate([rng.integers(0, W * H, 300), np.arange(W * H - W, W * H)]))
+    of, od, dm = oracle.fit_grid(pts, vals, grid, basis=basis, h=h, pixels=pix)
+    check("f64", F[:, pix], deg[pix], of, od, dm, vals)
+    P, V = torch_dev.from_numpy(pts).cuda(), torch_dev.from_numpy(vals).cuda()
+    G, slopes, gdeg = api.fit_grad(P, V, grid, basis=basis, h=h)
+    assert np.array_equal(G.cpu().numpy().reshape(d, -1).view(np.uint32), F.view(np.uint32))
+    assert np.array_equal(gdeg.cpu().numpy().ravel(), deg)
+    assert bool(slopes.isfinite().all())
+
+
+@pytest.mark.parametrize("basis,d", [("linear", 2), ("linear", 6), ("quadratic", 2)])
+def test_f64_moments_from_beyond_reach(torch_dev, oracle, basis, d):
+    """Nodes exactly on a point, and on their tile's anchor (no shift between
+    the frames, which would round such moments away), whose neighbours are 12 h
+    away: their first moments come from weights of e^-144 alone, far beyond the
+    reach, and the ladder accepts what those give (the tile is summed again
+    over all points)."""
+    note(f"case f64 beyond reach {basis} d={d}")
+    h = 1.0 / 128
+    dx = 1.5 * h
+    c, r = 8 + 16 * np.arange(3), 2 + 8 * np.arange(5)
+    pts = (np.stack(np.meshgrid(c, r), -1).reshape(-1, 2) * dx).astype(np.float32)
+    vals = np.random.default_rng(4).random((pts.shape[0], d)).astype(np.float32)
+    grid = {"x0": 0.0, "y0": 0.0, "dx": dx, "dy": dx, "width": 48, "height": 44}
+    kw = dict(basis=basis, h=h)
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, **kw)
+    of, od, dm = oracle.fit_grid(pts, vals, grid, **kw)
+    on = (r[:, None] * 48 + c[None, :]).ravel()
+    assert (od.ravel()[on] > 0).all() and np.array_equal(deg[on], od.ravel()[on])
+    check("f64", F, deg, of.reshape(d, -1), od.ravel(), dm.ravel(), vals)
+
+
+@pytest.mark.parametrize("n", [40, 1100])
+def test_f64_zero_floor_far_from_the_points(torch_dev, oracle, n):
+    """With a weight floor of 0 nodes 18 h and more from every point are
+    determined by weights of e^-324 and less."""
+    note(f"case f64 zero floor n={n}")
+    rng = np.random.default_rng(n)
+    pts = (rng.random((n, 2)) * 0.1).astype(np.float32)
+    vals = rng.random((n, 3)).astype(np.float32)
+    grid = {"x0": 1.0, "y0": 0.0, "dx": 0.01, "dy": 0.01, "width": 20, "height": 20}
+    kw = dict(basis="constant", h=0.05, weight_floor=0.0)
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, **kw)
+    of, od, dm = oracle.fit_grid(pts, vals, grid, **kw)
+    assert (deg == 0).all() and (od == 0).all()
+    check("f64", F, deg, of.reshape(3, -1), od.ravel(), dm.ravel(), vals)
+
+
+@pytest.mark.parametrize("n", [800, 9000])
+def test_f64_not_finite(torch_dev, n):
+    """As test_not_finite, with values that every tile looks through itself
+    and with more."""
+    from paper_1408_0677_amd import workloads as wl
+    note(f"case f64 not finite n={n}")
+    rng = np.random.default_rng(5)
+    pts = np.vstack([wl.uniform_points(rng, n), [[50.0, 50.0]]]).astype(np.float32)
+    vals = wl.smooth_fields(rng, pts, 5).astype(np.float32)
+    grid = {"x0": 0.2, "y0": 0.2, "dx": 0.004, "dy": 0.004, "width": 40, "height": 24}
+    kw = dict(basis="linear", h=0.08)
+    F0, d0 = gpu_fit(torch_dev, pts, vals, grid, **kw)
+    bad = vals.copy()
+    bad[-1, 1] = np.nan
+    F1, d1 = gpu_fit(torch_dev, pts, bad, grid, **kw)
+    others = [0, 2, 3, 4]
+    assert np.isnan(F1[1]).all() and np.isfinite(F1[others]).all()
+    assert np.array_equal(d0, d1)
+    # all points summed, in the same order: the float64 sums' rounding only
+    assert np.abs(F1[others] - F0[others]).max() <= 1e-6 * np.abs(F0).max()
+    inf = pts.copy()
+    inf[-1] = [np.inf, 0.0]
+    F2, d2 = gpu_fit(torch_dev, inf, vals, grid, **kw)
+    assert (d2 == 0).all() and np.isnan(F2).all()
 
 
 @pytest.mark.parametrize("prec,d", [("fp16", 3), ("bf16", 3), ("bf16", 40)])
