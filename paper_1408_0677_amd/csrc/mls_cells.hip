@@ -21,7 +21,11 @@
 // node tiles by descending list length, so that the heavy tiles of dense
 // clusters start first; the order keeps 4 x 4 supertiles of neighbouring
 // tiles together on one XCD, so that their shared points stay in its L2.
-// All of it is bound by HBM and launch latency, not arithmetic.
+// All of it is bound by HBM and launch latency, not arithmetic, so small sets
+// take as few launches as the order of the points allows: scans of up to
+// 16,384 values and the tile order of up to 4,096 supertiles are one
+// workgroup each, and one kernel gathers everything.  20,011 points, 777 x
+// 513: 198 us of staging and lists before, 90 now.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -91,6 +95,38 @@ __global__ __launch_bounds__(256) void scan_blocks_u32_kernel(uint32_t* v, int64
   if (t == 0) sums[blockIdx.x] = tot;
 }
 
+// The whole scan in one workgroup, for up to kScanOne values: 16 per thread,
+// in registers.
+constexpr int kScanOne = 16384;
+
+__global__ __launch_bounds__(1024) void scan_one_u32_kernel(uint32_t* v, int count) {
+  __shared__ uint32_t wsum[16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int base = 16 * t;
+  uint32_t x[16], sum = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    x[q] = base + q < count ? v[base + q] : 0u;
+    sum += x[q];
+  }
+  uint32_t incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t nb = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += nb;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - sum;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) run += w < wave ? wsum[w] : 0u;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    if (base + q < count) v[base + q] = run;
+    run += x[q];
+  }
+}
+
 __global__ __launch_bounds__(256) void scan_add_u32_kernel(uint32_t* v, int64_t count,
                                                            const uint32_t* sums) {
   __shared__ uint32_t wsum[4];
@@ -125,15 +161,14 @@ __global__ __launch_bounds__(kSortThreads) void radix_downsweep_kernel(
     const uint32_t d = valid ? digit_of(key, shift) : 0xFFFFFFFFu;
     for (int q = t; q < 4 * kDigits; q += kSortThreads) (&wave_cnt[0][0])[q] = 0;
     __syncthreads();
-    // peers: lanes of this wave with the same digit
-    uint64_t remaining = __ballot(valid);
-    uint64_t peers = 0;
-    while (remaining) {
-      const int leader = __ffsll((unsigned long long)remaining) - 1;
-      const uint32_t ld = __shfl(d, leader, 64);
-      const uint64_t m = __ballot(d == ld) & remaining;
-      if (d == ld) peers = m;
-      remaining &= ~m;
+    // peers: lanes of this wave with the same digit, by a ballot per bit
+    // (taking the digits present one by one, up to 64 of them with a lane
+    // shuffle each, made the pass 20 us instead of 9.6 at 20,000 keys)
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < 8; ++bit) {
+      const uint64_t set = __ballot((d >> bit) & 1u);
+      peers &= (d >> bit) & 1u ? set : ~set;
     }
     const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const uint32_t rank_in_wave = (uint32_t)__popcll(peers & lt);
@@ -178,42 +213,30 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, int64_t n, u
   if (i < n) p[i] = v;
 }
 
-// cell_start from the sorted cell ids: the first point of each run of ids
-// writes its index into the start of every cell from the previous run's id
-// + 1 up to its own (empty cells between take the same start); the last
-// point closes the cells after it.  No atomics.
-__global__ __launch_bounds__(256) void cell_start_kernel(const uint32_t* sorted_keys, int64_t n,
-                                                         int64_t ncells, uint32_t* cell_start) {
+// Sorted payload: the attribute-major normalised values of attribute
+// blockIdx.y, and from the first row of workgroups the coordinates and
+// cell_start.  cell_start comes from the sorted cell ids: the first point of
+// each run of ids writes its index into the start of every cell from the
+// previous run's id + 1 up to its own (empty cells between take the same
+// start); the last point closes the cells after it.  No atomics.
+__global__ __launch_bounds__(256) void gather_kernel(const float* pts, const float* vals_t,
+                                                     const uint32_t* sorted_keys,
+                                                     const uint32_t* perm, int64_t n,
+                                                     int64_t ncells, float* pts_s,
+                                                     float* vals_ts, uint32_t* cell_start) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int d = blockIdx.y;
   if (i >= n) return;
+  const int64_t j = perm[i];
+  vals_ts[(int64_t)d * n + i] = vals_t[(int64_t)d * n + j];
+  if (d > 0) return;
+  pts_s[2 * i] = pts[2 * j];
+  pts_s[2 * i + 1] = pts[2 * j + 1];
   const int64_t k = sorted_keys[i];
   const int64_t prev = i == 0 ? -1 : (int64_t)sorted_keys[i - 1];
   for (int64_t c = prev + 1; c <= k; ++c) cell_start[c] = (uint32_t)i;
   if (i == n - 1)
     for (int64_t c = k + 1; c <= ncells; ++c) cell_start[c] = (uint32_t)n;
-}
-
-// Sorted payload: coordinates and the attribute-major normalised values.
-__global__ __launch_bounds__(256) void gather_points_kernel(const float* pts, const uint32_t* perm,
-                                                            int64_t n, float* pts_s) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  const int64_t j = perm[i];
-  pts_s[2 * i] = pts[2 * j];
-  pts_s[2 * i + 1] = pts[2 * j + 1];
-}
-
-__global__ __launch_bounds__(256) void gather_values_kernel(const float* vals_t, const uint32_t* perm,
-                                                            int64_t n, int D, float* vals_ts) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int d = blockIdx.y;
-  if (i >= n) return;
-  vals_ts[(int64_t)d * n + i] = vals_t[(int64_t)d * n + perm[i]];
-}
-
-__global__ __launch_bounds__(256) void iota_u32_kernel(uint32_t* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = (uint32_t)i;
 }
 
 // Work of each 4 x 4 supertile (the sum of its tiles' list lengths, from
@@ -285,18 +308,32 @@ __global__ __launch_bounds__(256) void tile_list_kernel(const uint32_t* cell_sta
   const uint64_t below = (1ull << lane) - 1ull;
   int64_t out = list ? (int64_t)tile_start[tile] : 0;
   uint32_t cnt = 0;
+  // the points of a row of cells, the next 64 in flight during a test; the
+  // next row's bounds are requested before this row is walked
+  uint32_t a1 = 0, b1 = 0;
+  if (cy0 <= cy1) {
+    a1 = cell_start[cy0 * ncx + cx0];
+    b1 = cell_start[cy0 * ncx + cx1 + 1];
+  }
   for (int cy = cy0; cy <= cy1; ++cy) {
-    const int64_t a = cell_start[cy * ncx + cx0];
-    const int64_t b = cell_start[cy * ncx + cx1 + 1];
+    const int64_t a = a1, b = b1;
+    if (cy < cy1) {
+      a1 = cell_start[(cy + 1) * ncx + cx0];
+      b1 = cell_start[(cy + 1) * ncx + cx1 + 1];
+    }
+    const float2* row = (const float2*)pts_s;
+    // past the end the last point of the list again
+    auto at = [&](int64_t k) { return row[k < b ? k : b - 1]; };
+    if (a >= b) continue;
+    float2 next = at(a + lane);
     for (int64_t k0 = a; k0 < b; k0 += 64) {
       const int64_t k = k0 + lane;
-      bool in = false;
-      if (k < b) {
-        const double x = (double)pts_s[2 * k], y = (double)pts_s[2 * k + 1];
-        const double ex = fmax(fmax(xlo - x, x - xhi), 0.0);
-        const double ey = fmax(fmax(ylo - y, y - yhi), 0.0);
-        in = ex * ex + ey * ey < reach2;
-      }
+      const float2 pt = next;
+      if (k0 + 64 < b) next = at(k + 64);
+      const double x = (double)pt.x, y = (double)pt.y;
+      const double ex = fmax(fmax(xlo - x, x - xhi), 0.0);
+      const double ey = fmax(fmax(ylo - y, y - yhi), 0.0);
+      const bool in = k < b && ex * ex + ey * ey < reach2;
       const uint64_t m = __ballot(in);
       if (list && in) {
         const int64_t o = out + __popcll(m & below);
@@ -308,7 +345,63 @@ __global__ __launch_bounds__(256) void tile_list_kernel(const uint32_t* cell_sta
   }
   if (!list && lane == 0) {
     counts[tile] = cnt;
+    if (tile == tiles - 1) counts[tiles] = 0;   // the scan leaves the total there
     keys[tile] = 0xFFFFFFFFu - cnt;
+  }
+}
+
+// The tile order of up to kOrderSupers supertiles in one workgroup: work of
+// each supertile, a bitonic sort of (descending work, supertile) in LDS, and
+// the workgroup slots.  The order is that of the three kernels above with the
+// radix sort between them (ties by supertile), whose 20 launches cost about
+// 85 us whatever the size.
+constexpr int kOrderSupers = 4096;
+
+__global__ __launch_bounds__(1024) void tile_order_kernel(const uint32_t* tile_start, int tiles_x,
+                                                          int tiles_y, int super_x, int nsuper,
+                                                          int size, uint32_t* torder) {
+  __shared__ uint64_t key[kOrderSupers];
+  constexpr int kPer = kSuperTile * kSuperTile;
+  const int t = threadIdx.x;
+  // the tiles of a supertile's row are consecutive, so two starts give their
+  // work; all eight loads of a supertile in flight
+  for (int s = t; s < size; s += 1024) {
+    const int tc = (s % super_x) * kSuperTile, tr = (s / super_x) * kSuperTile;
+    const int tc1 = tc + kSuperTile < tiles_x ? tc + kSuperTile : tiles_x;
+    uint64_t work = 0;
+#pragma unroll
+    for (int r = 0; r < kSuperTile; ++r)
+      if (s < nsuper && tr + r < tiles_y)
+        work += tile_start[(tr + r) * tiles_x + tc1] - tile_start[(tr + r) * tiles_x + tc];
+    const uint32_t w = work > 0xFFFFFFFEull ? 0xFFFFFFFEu : (uint32_t)work;
+    key[s] = s < nsuper ? ((uint64_t)(0xFFFFFFFFu - w) << 32) | (uint32_t)s : ~0ull;
+  }
+  __syncthreads();
+  for (int k = 2; k <= size; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int e = t; e < size / 2; e += 1024) {
+        const int a = 2 * e - (e & (j - 1)), b = a + j;   // the pair of element e
+        const uint64_t x = key[a], y = key[b];
+        if ((x > y) == ((a & k) == 0)) {
+          key[a] = y;
+          key[b] = x;
+        }
+      }
+      __syncthreads();
+    }
+  // supertile of rank j goes to XCD j % 8 (tile_slots_kernel); the ranks up
+  // to a multiple of eight without a supertile are empty slots
+  const int ranks = (nsuper + 7) / 8 * 8;
+  for (int i = t; i < ranks * kPer; i += 1024) {
+    const int j = i / kPer, k = i % kPer;
+    uint32_t tile = 0xFFFFFFFFu;
+    if (j < nsuper) {
+      const int s = (int)(uint32_t)key[j];
+      const int tc = (s % super_x) * kSuperTile + k % kSuperTile;
+      const int tr = (s / super_x) * kSuperTile + k / kSuperTile;
+      if (tc < tiles_x && tr < tiles_y) tile = (uint32_t)(tr * tiles_x + tc);
+    }
+    torder[8 * (kPer * (j / 8) + k) + j % 8] = tile;
   }
 }
 
@@ -335,6 +428,10 @@ int64_t scan_sums_words(int64_t count) { return (count + kScanBlock - 1) / kScan
 hipError_t scan_u32(uint32_t* v, int64_t count, uint32_t* sums, hipStream_t s) {
   const unsigned nb = (unsigned)scan_sums_words(count);
   if (nb == 0) return hipSuccess;
+  if (count <= kScanOne) {
+    hipLaunchKernelGGL(scan_one_u32_kernel, dim3(1), dim3(1024), 0, s, v, (int)count);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(scan_blocks_u32_kernel, dim3(nb), dim3(256), 0, s, v, count, sums);
   hipLaunchKernelGGL(scan_add_u32_kernel, dim3(nb), dim3(256), 0, s, v, count,
                      (const uint32_t*)sums);
@@ -375,15 +472,10 @@ hipError_t launch_cells(const CellArgs& a, hipStream_t s) {
   if (bits < 8) bits = 8;
   hipError_t e = radix_sort_pairs(a.keys, a.perm, a.keys2, a.perm2, n, bits, a.hist, a.ssum, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cell_start_kernel, dim3(gb), dim3(256), 0, s, a.keys, n, (int64_t)ncells,
-                     a.cell_start);
-  hipLaunchKernelGGL(gather_points_kernel, dim3(gb), dim3(256), 0, s, a.pts, a.perm, n, a.pts_s);
-  hipLaunchKernelGGL(gather_values_kernel, dim3(gb, a.D), dim3(256), 0, s, a.vals_t, a.perm, n,
-                     a.D, a.vals_ts);
+  hipLaunchKernelGGL(gather_kernel, dim3(gb, a.D), dim3(256), 0, s, a.pts, a.vals_t, a.keys,
+                     a.perm, n, (int64_t)ncells, a.pts_s, a.vals_ts, a.cell_start);
   // per-tile point lists: counts (and the work keys), starts, entries
   const unsigned lb = (unsigned)((a.tiles + 3) / 4);
-  hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((a.tiles + 1 + 255) / 256)), dim3(256), 0,
-                     s, a.tile_start, (int64_t)a.tiles + 1, 0u);
   hipLaunchKernelGGL(tile_list_kernel, dim3(lb), dim3(256), 0, s, a.cell_start, a.pts_s, a.ncx,
                      a.ncy, a.geom, a.tiles_x, a.tiles, a.tile_start, a.tkeys,
                      (const uint32_t*)nullptr, (uint32_t*)nullptr, (int64_t)0);
@@ -395,6 +487,13 @@ hipError_t launch_cells(const CellArgs& a, hipStream_t s) {
   const int tiles_y = a.tiles / a.tiles_x;
   const int super_x = (a.tiles_x + kSuperTile - 1) / kSuperTile;
   const int nsuper = super_x * ((tiles_y + kSuperTile - 1) / kSuperTile);
+  if (nsuper <= kOrderSupers) {
+    int size = 64;   // a power of two, as the sort needs
+    while (size < nsuper) size <<= 1;
+    hipLaunchKernelGGL(tile_order_kernel, dim3(1), dim3(1024), 0, s, a.tile_start, a.tiles_x,
+                       tiles_y, super_x, nsuper, size, a.torder);
+    return hipGetLastError();
+  }
   const int64_t slots = tile_order_slots(a.tiles_x, tiles_y);
   hipLaunchKernelGGL(supertile_work_kernel, dim3((unsigned)((nsuper + 255) / 256)), dim3(256), 0,
                      s, a.tile_start, a.tiles_x, tiles_y, super_x, nsuper, a.tkeys, a.sorder);
