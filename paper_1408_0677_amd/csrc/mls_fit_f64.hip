@@ -237,7 +237,7 @@ void fit_f64_kernel(F64Params p) {
   base = pos;
   if (LIST) {
     cnt = list_points<kThreads, kListCap>(
-        p.pts, p.n, pos, lds_list, [&](float x, float y) { return in_reach(reach, x, y); });
+        p.pts, p.n, pos, (LdsBytes)lds_list, [&](float x, float y) { return in_reach(reach, x, y); });
   } else {
     cnt = pos = p.n;
   }

@@ -99,7 +99,7 @@ void fit_f64_shape_kernel(F64Params p) {
   auto next_list = [&](int64_t& pos) {
     base = pos;
     kept = list_points<kThreads, kListCap>(
-        p.pts, p.n, pos, lds_list, [&](float x, float y) { return in_reach(reach, x, y); });
+        p.pts, p.n, pos, (LdsBytes)lds_list, [&](float x, float y) { return in_reach(reach, x, y); });
   };
 
   // raw data of a chunk, one chunk ahead in registers

@@ -48,14 +48,16 @@
 // only.  With the Wendland weight that is the tile's list of cell-sorted
 // points (mls_cells.hip).  With the Gaussian the tile first tests every point
 // against its own reach and lists the ones inside in LDS (list_points): a
-// point outside carries features that are exactly zero (or, in float16,
-// weights that round to zero), so the sums are those over all points.  The
-// test costs a point 8 bytes of L2 and a few instructions per tile, against
-// about 2 us of a compute unit per 64 points contracted.  A fit's listed
-// share of the points is about pi (8.4 h)^2 of the unit square (bfloat16)
-// or pi (5.5 h)^2 (float16): 50,000 points, 64 attributes, h = 0.015, 2048^2
-// (bfloat16, two passes) 206.3 -> 14.3 ms; 7,351 points, 19 attributes,
-// 701 x 643 (float16) 3.81 -> 0.86 ms.
+// point outside carries features that are exactly zero, or weights that round
+// to zero (float16) or that no sum can see (bfloat16, in_reach and
+// list_adaptive).  The test costs a point 8 bytes of L2 and a few
+// instructions per tile, against about 2 us of a compute unit per 64 points
+// contracted.  50,000 points, 64 attributes, h = 0.015, 2048^2 (bfloat16, two
+// passes): 206.3 ms over all points, 14.2 within 8 h (39 chunks a pass), 9.6
+// within the adaptive reach (25).  There a tile takes 350,000 cycles: 42,000
+// of listing, 87,000 of pass 1, 13,000 of solves, 185,000 of pass 2, 18,000 of
+// stores; in pass 2 the vector instructions of the effective weights and the
+// producers bound it, the matrix instructions are a fifth.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -83,6 +85,7 @@ struct LPParams {
   float cutoff2;          // points with u^2 beyond this get no features
   float reach2;           // ... and their weight rounds to zero (float16) beyond this
                           // squared distance (in h^2) from the tile's nodes
+  float list_log;         // ln n + 36 ln 2 (bfloat16: reach_sq)
   float* fields;
   uint8_t* deg_out;
   float* grads;           // [D][2][H][W] or null
@@ -110,8 +113,13 @@ hipError_t launch_lp_bf16(const LPParams& p, int deg, int nts, int terms, hipStr
 hipError_t launch_lp_fp16(const LPParams& p, int deg, int nts, int terms, hipStream_t s);
 hipError_t launch_lp_wend_bf16(const LPParams& p, int deg, int nts, int terms, hipStream_t s);
 hipError_t launch_lp_wend_fp16(const LPParams& p, int deg, int nts, int terms, hipStream_t s);
-hipError_t launch_lp_shape(const LPParams& p, int deg, int ntv, int terms, hipStream_t s);
-hipError_t launch_lp_batch(const LPBatch& b, bool fp16, int deg, int nts, int grid, hipStream_t s);
+hipError_t launch_shape_bf16(const LPParams& p, int deg, int ntv, int terms, hipStream_t s);
+hipError_t launch_shape_fp16(const LPParams& p, int deg, int ntv, int terms, hipStream_t s);
+hipError_t launch_batch_bf16(const LPBatch& b, int deg, int nts, int grid, hipStream_t s);
+hipError_t launch_batch_fp16(const LPBatch& b, int deg, int nts, int grid, hipStream_t s);
+// Batch classes of the two-pass form: kBatchShape + attribute tiles in the
+// place of the feature tiles.
+constexpr int kBatchShape = 8;
 
 namespace {
 
@@ -285,6 +293,17 @@ __device__ __forceinline__ float wendland_c2(float s2) {
 // The reach of a tile's nodes in the tile frame (units of h): a point adds
 // nothing beyond `cut2` from the anchor, nor beyond `reach2` from the
 // rectangle [xlo, xhi] x [ylo, yhi] of the nodes.
+// With bfloat16, which has float32's range, a second test follows from what
+// the sums can see (adaptive reach).  The points beyond R h of every node add
+// at most n exp(-R^2) R^(2 DEG) to any node's sum of w b_j^2.  R is chosen so
+// that this is 2^-36 of the larger of the weight floor and a lower bound S of
+// the tile's weight sums: 4,096 times less than the rounding of float32 sums.
+// Every sum leaves out the same points, so the fit is that of the weight cut
+// to zero there.  Where a node's smallest diagonal moment is below 2^-12 of
+// that scale, so that what is left out could be above 2^-24 of it, the tile is
+// summed again without this test.
+constexpr float kDiagFloor = 0x1p-12f;
+
 struct TileReach {
   float cxr, cyr, inv_h, cut2, reach2, xlo, xhi, ylo, yhi;
 };
@@ -299,6 +318,27 @@ __device__ __forceinline__ TileReach tile_reach(const LPParams& p, int c0, int r
                    fminf(ya, yb), fmaxf(ya, yb)};
 }
 
+// R^2 for a weight sum of at least S, rounded up to a 64th.
+template <int DEG>
+__device__ __forceinline__ float reach_sq(float list_log, float scale) {
+#pragma clang fp contract(off)
+  if (!(scale > 0.0f)) return __builtin_inff();
+  const float L = list_log - __logf(scale);
+  float r2 = L;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) r2 = L + (float)DEG * __logf(r2);
+  return ceilf(r2 * 64.0f) * 0.015625f;
+}
+
+// The weight of a point at its farthest node of the tile.
+__device__ __forceinline__ float far_weight(const TileReach& t, float x, float y) {
+#pragma clang fp contract(off)
+  const float ux = (x - t.cxr) * t.inv_h, uy = (y - t.cyr) * t.inv_h;
+  const float ex = fmaxf(fabsf(ux - t.xlo), fabsf(ux - t.xhi));
+  const float ey = fmaxf(fabsf(uy - t.ylo), fabsf(uy - t.yhi));
+  return __expf(-(ex * ex + ey * ey));
+}
+
 // Whether the tile must take the point at (x, y).  The anchor test is the
 // one the producers zero features by, with room for its rounding; a
 // coordinate that is not finite (or whose square overflows) is kept, since
@@ -311,7 +351,85 @@ __device__ __forceinline__ bool in_reach(const TileReach& t, float x, float y) {
   const float u2 = ux * ux + uy * uy;
   const float ex = fmaxf(fmaxf(t.xlo - ux, ux - t.xhi), 0.0f);
   const float ey = fmaxf(fmaxf(t.ylo - uy, uy - t.yhi), 0.0f);
-  return (u2 <= t.cut2 * 1.0001f && ex * ex + ey * ey <= t.reach2) || !(u2 < __builtin_inff());
+  return ((u2 <= t.cut2 * 1.0001f) & (ex * ex + ey * ey <= t.reach2)) | !(u2 < __builtin_inff());
+}
+
+// The next list of a tile's points with the adaptive reach.  Most points of a
+// call are far from a tile, so all are tested against a rectangle only, in the
+// points' own coordinates (widened by what their rounding and that of its
+// middle can be), and the few listed ones against in_reach.  While the reach
+// applies (`cut`), the rectangle is that of the reach that the weight floor
+// alone gives; the listed points' weights at the farthest node add up to S,
+// and the list is cut to the reach that S gives (S of one list is a lower
+// bound as well).  Every kernel that lists a request's points must come to the
+// same list.
+//
+// A call, not inlined: its masks and predicates took registers from the loops
+// around it (the quadratic two-pass kernel spilled 81 vector and 112 scalar
+// registers with its copies, 22 and 50 without).
+struct ListedPoints {
+  int cnt, taken;   // entries; points of the input that they were chosen from
+  float scale;
+};
+
+template <int DEG>
+__device__ __noinline__ ListedPoints list_adaptive(const float* points, int64_t n, int64_t at,
+                                                   float list_log, float floor_w, TileReach t,
+                                                   int cut, LdsBytes lds_list) {
+#pragma clang fp contract(off)
+  // arguments come in vector registers
+  points = uniform(points);
+  n = uniform(n);
+  at = uniform(at);
+  list_log = uniform(list_log);
+  floor_w = uniform(floor_w);
+  t = uniform(t);
+  cut = uniform(cut);
+  lds_list = uniform(lds_list);
+  float scale = __builtin_inff();
+  int64_t pos = at;
+  if (cut) t.reach2 = reach_sq<DEG>(list_log, floor_w);
+  const float R = __builtin_amdgcn_sqrtf(t.reach2), C = __builtin_amdgcn_sqrtf(t.cut2) * 1.001f;
+  const float xm = 0.5f * (t.xlo + t.xhi), ym = 0.5f * (t.ylo + t.yhi);
+  const float h = __builtin_amdgcn_rcpf(t.inv_h) * 1.001f;
+  const float mx = t.cxr + xm * h, my = t.cyr + ym * h;
+  const float bx = (fminf(0.5f * (t.xhi - t.xlo) + R, C + fabsf(xm)) + 0.01f * fabsf(xm)) * h +
+                   0x1p-20f * fabsf(mx);
+  const float by = (fminf(0.5f * (t.yhi - t.ylo) + R, C + fabsf(ym)) + 0.01f * fabsf(ym)) * h +
+                   0x1p-20f * fabsf(my);
+  const float far = 1e18f * h;   // short of where a square overflows in units of h
+  int cnt = list_points<kThreads, kListCap>(points, n, pos, lds_list, [&](float x, float y) {
+    const float ax = fabsf(x - mx), ay = fabsf(y - my);
+    return ((ax <= bx) & (ay <= by)) | !(ax + ay < far);
+  });
+  cnt = refine_list<kThreads, kListCap>(
+      points, at, cnt, lds_list, [&](float x, float y) { return far_weight(t, x, y); },
+      [&](float x, float y, float S) {
+        if (cut) {
+          // a NaN (a point that is not finite) leaves the floor
+          scale = fmaxf(0.99f * S, floor_w);
+          t.reach2 = reach_sq<DEG>(list_log, scale);
+        }
+        return in_reach(t, x, y);
+      });
+  return ListedPoints{cnt, (int)(pos - at), scale};
+}
+
+// The next list of a tile's points from `pos` on; `scale` keeps the smallest
+// scale of the adaptive reach.
+template <int DEG, bool ADAPT>
+__device__ __forceinline__ int next_points(const LPParams& p, const TileReach& t, bool cut,
+                                           int64_t& pos, char* lds_list, float& scale) {
+  if constexpr (ADAPT) {
+    const ListedPoints l = list_adaptive<DEG>(p.pts, p.n, pos, p.list_log, (float)p.floor_w, t,
+                                              cut, (LdsBytes)lds_list);
+    pos += __builtin_amdgcn_readfirstlane(l.taken);
+    scale = fminf(scale, uniform(l.scale));
+    return __builtin_amdgcn_readfirstlane(l.cnt);
+  } else {
+    return list_points<kThreads, kListCap>(p.pts, p.n, pos, (LdsBytes)lds_list,
+                                           [&](float x, float y) { return in_reach(t, x, y); });
+  }
 }
 
 // Producer: global -> registers for one raw chunk, its attributes
@@ -547,6 +665,27 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
   auto tab = [&](int b) { return (float*)(lds_lp + L::kTab0 + b * L::kTabB); };
   auto raw = [&](int b) { return (float*)(lds_lp + L::kRaw0 + b * L::kRawB); };
 
+  // The tile's points, a list at a time: the whole cell list (Wendland), or
+  // segments of the points in reach (Gaussian).  Matrix and producer waves
+  // run separate loops with the same barriers, so that neither holds the
+  // other's registers.
+  const uint16_t* list = (const uint16_t*)(lds_lp + L::kList0);
+  const TileReach reach = CELLS ? TileReach{} : tile_reach(p, c0, r0, cxr, cyr);
+  // Adaptive reach: whether it still applies, and the scale it was chosen by.
+  constexpr bool ADAPT = !CELLS && __is_same(T, __bf16);
+  bool cut = ADAPT;
+  float scale = __builtin_inff();
+  auto next_list = [&](int64_t& pos, Walker& wk) {
+    if (CELLS) {
+      wk.k = (int64_t)p.tile_start[tile];
+      wk.kend = (int64_t)p.tile_start[tile + 1];
+      pos = p.n;
+    } else {
+      wk.k = 0;
+      wk.kend = next_points<DEG, ADAPT>(p, reach, cut, pos, lds_lp + L::kList0, scale);
+    }
+  };
+  for (;;) {
   // feature rows past this slab's F are never written: zero them once in
   // both buffers
   {
@@ -558,24 +697,11 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
         for (int e = tid; e < pad; e += kThreads) z[e] = (T)0.0f;
       }
   }
-  // The tile's points, a list at a time: the whole cell list (Wendland), or
-  // segments of the points in reach (Gaussian).  Matrix and producer waves
-  // run separate loops with the same barriers, so that neither holds the
-  // other's registers.
-  const uint16_t* list = (const uint16_t*)(lds_lp + L::kList0);
-  const TileReach reach = CELLS ? TileReach{} : tile_reach(p, c0, r0, cxr, cyr);
-  auto next_list = [&](int64_t& pos, Walker& wk) {
-    if (CELLS) {
-      wk.k = (int64_t)p.tile_start[tile];
-      wk.kend = (int64_t)p.tile_start[tile + 1];
-      pos = p.n;
-    } else {
-      wk.k = 0;
-      wk.kend = list_points<kThreads, kListCap>(
-          p.pts, p.n, pos, lds_lp + L::kList0,
-          [&](float x, float y) { return in_reach(reach, x, y); });
-    }
-  };
+  // the first list, mostly the only one, by code that all waves share (their
+  // own copies of it would each come from the L2 once per tile)
+  int64_t base = 0, pos = 0;
+  Walker wk;
+  next_list(pos, wk);
   floatx4 acc[R][NTS];
   if (mma) {
 #pragma unroll
@@ -584,9 +710,7 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
       for (int q = 0; q < NTS; ++q) acc[t][q] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int i = lane & 15;
     const int k8 = (lane >> 4) * 8;   // this lane's 8 points of a 32-point k-step
-    for (int64_t pos = 0; pos < p.n;) {
-      Walker wk;
-      next_list(pos, wk);
+    for (;;) {
       __syncthreads();   // raw 0 and 1
       __syncthreads();   // chunk 0
       int c = 0;
@@ -637,15 +761,20 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
         }
         __syncthreads();
       }
+      if (pos >= p.n) break;
+      next_list(pos, wk);
     }
   } else {
+    // (made again where the tile is summed again: held over the solve, what
+    // follows from the thread's index takes more registers than there are)
+    int ptl = pt;
+    if (ADAPT) asm volatile("" : "+v"(ptl));
+    __builtin_assume(ptl >= 0 && ptl < kProd);
+    const int pt = ptl;
     float toff[kTabIt];
-    table_offsets(p, pt, c0, r0, cxr, cyr, toff);
     const RowWalk rw = row_walk(pt, Ds);
-    for (int64_t pos = 0; pos < p.n;) {
-      const int64_t base = pos;
-      Walker wk;
-      next_list(pos, wk);
+    bool first = true;
+    for (;;) {
       Chunk ch0 = walker_take(wk);
       Chunk ch1 = walker_take(wk);
       float rr[L::kRawIt], rxy = 0.0f;
@@ -662,10 +791,15 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
                                          cyr);
       };
       // raw 0 and 1 to LDS, then chunk 0's tables and features
+      float r1[L::kRawIt], rxy1 = 0.0f;
       load(ch0);
+      if (CELLS) raw_load_cells(p, ch1, d0, Ds, pt, r1);
+      else raw_load_rows(p, ch1, base, list, d0, Ds, rw, pt, r1, rxy1);
+      if (first) table_offsets(p, pt, c0, r0, cxr, cyr, toff);   // loads in flight
+      first = false;
       store(0);
-      load(ch1);
-      store(1);
+      if (CELLS) raw_store_cells(raw(1), Ds, pt, r1);
+      else raw_store_rows(raw(1), Ds, rw, pt, r1, rxy1);
       __syncthreads();
       if (ch0.valid) make(ch0, 0);
       __syncthreads();
@@ -678,6 +812,9 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
         ch0 = ch1;
         ch1 = ch2;
       }
+      if (pos >= p.n) break;
+      base = pos;
+      next_list(pos, wk);
     }
   }
 
@@ -700,6 +837,7 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
   __syncthreads();
   // one node per lane on the first four waves (one per SIMD): the float64
   // solve is issued by four full waves rather than eight half-empty ones
+  bool low = false;
   if (tid < kRows * kCols) {
     const int w = tid / (16 * R), local = tid % (16 * R);
     const float* e = epi + (w * 16 * R + local) * L::kEpiStride;
@@ -710,15 +848,22 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
       const double ex = node_offset_xd(p, c0, col, cxr);
       const double ey = node_offset_yd(p, r0, w * R + t, cyr);
       const int64_t off = (int64_t)r * p.W + cc;
+      double diag;
       uint8_t code = solve_node<DEG, float>(e, Ds, ex, ey, p.tau, p.floor_w,
                                             p.fields + (int64_t)d0 * plane + off, plane,
                                             p.shift + d0, p.scale + d0,
                                             (double)WeightGain<T>::value,
                                             p.grads ? p.grads + (int64_t)(2 * d0) * plane + off
                                                     : nullptr,
-                                            p.inv_hd);
+                                            p.inv_hd, ADAPT ? &diag : nullptr);
+      low = ADAPT && diag < (double)(scale * kDiagFloor);
       if (p.deg_out && slab == 0) p.deg_out[off] = code;
     }
+  }
+  // once more without the adaptive reach where a node could see past it
+  if (!ADAPT || !cut) break;
+  if (!__syncthreads_or(low)) break;
+  cut = false;
   }
 }
 
@@ -726,6 +871,597 @@ template <int DEG, int NTS, int S, typename T, bool WEND, bool CELLS>
 __global__ __launch_bounds__(kThreads) void fit_lp_kernel(LPParams p) {
   extern __shared__ __attribute__((aligned(16))) char lds_lp[];
   lp_tile<DEG, NTS, S, T, WEND, CELLS>(p, blockIdx.x, lds_lp);
+}
+
+// ---------------------------------------------------------------------------
+// Two-pass (shape-function) form of the same fit with the Gaussian weight.
+// The field at node p is
+//   field_d(p) = y_p^T R_t,d = sum_i w_ip (y_p^T b_t(u_i)) f_i,d,
+// y_p = T'^T M_p'^{-1} e_0 the tile-frame coefficients of the node's shape
+// function (mls_solve.h).  Pass 1 contracts the weights with the moment
+// monomials only (one 16-column feature tile, S1 terms, split weight) and
+// solves every node's ladder for y_p; pass 2 streams the points again and
+// contracts the effective weights w_ip (y_p^T b_t(u_i)), formed per pair in
+// float32 and split hi + lo, with the attributes (two 16-bit terms each).
+// The contraction width falls from n_mom + m D to n_mom + D (399 -> 79 for
+// the quadratic basis with 64 attributes); the solve runs once per node and
+// attribute slab instead of per feature.  The error stays the float32
+// accumulation of the moments in pass 1: the effective weights and the
+// attribute terms add about 2^-16 (bfloat16) or 2^-22 (float16) relative per
+// pair, which is not amplified by the conditioning.
+//
+// float16 needs its range looked after.  The weights carry their gain 2^15
+// into pass 1, which leaves y_p 2^-15 of its size.  An effective weight is at
+// most sum_j |z_j| (z the node-frame coefficients, since |b_j(u)| exp(-u^2)
+// <= 1), so each node's y_p is scaled by the power of two that brings this
+// bound to 2^14 .. 2^15 (shape_scale); the attributes are scaled by 2^10 so
+// that the second term of a value near 0 keeps its digits.  The node's power
+// and the 2^10 are taken out of the float32 sum at the end, exactly.
+//
+// The producers run ahead of the solve: while the first four waves turn the
+// moments into y_p, they load the first two chunks of pass 2.
+// ---------------------------------------------------------------------------
+
+constexpr int kShapeDsCap = 64;    // attributes per workgroup slab
+constexpr int kShapeS2 = 2;        // 16-bit terms per attribute value
+template <typename T> struct AttrGain { static constexpr float value = 1.0f; };
+template <> struct AttrGain<_Float16> { static constexpr float value = 1024.0f; };
+
+template <int DEG, int NTV, int S1>
+struct ShapeLayout {
+  static constexpr int m = DEG == 1 ? 3 : 6;
+  static constexpr int nmom = DEG == 1 ? 6 : 15;
+  static constexpr int kRows1 = S1 * 16;                 // pass 1 feature rows
+  static constexpr int kRows2 = kShapeS2 * NTV * 16;     // pass 2 feature rows
+  static constexpr int kFeatRows = kRows1 > kRows2 ? kRows1 : kRows2;
+  static constexpr int kDs = NTV * 16;
+  static constexpr int kRawFloats = (2 + kDs) * RS;
+  static constexpr int kRawIt = (kDs * KT + kProd - 1) / kProd;
+  static constexpr int kFeatB = kFeatRows * KSH * 2;
+  static constexpr int kTabB = (kCols + kRows) * KSF * 4;
+  static constexpr int kBasB = 3 * KSF * 4;              // 1, u_x, u_y per point
+  static constexpr int kRawB = kRawFloats * 4;
+  static constexpr int kFeat0 = 0;
+  static constexpr int kTab0 = kFeat0 + 2 * kFeatB;
+  static constexpr int kBas0 = kTab0 + 2 * kTabB;
+  static constexpr int kRaw0 = kBas0 + 2 * kBasB;
+  static constexpr int kLoop = kRaw0 + 2 * kRawB;
+  // the moments between the passes, apart from the chunk buffers, which the
+  // producers fill for pass 2 meanwhile
+  static constexpr int kEpiStride = 16 + 1;
+  static constexpr int kEpi0 = kLoop;
+  static constexpr int kEpiB = kMmaWaves * 16 * R * kEpiStride * 4;
+  // per node: the shape coefficients y (float32), the factor that maps its
+  // sums back, and the degree code
+  static constexpr int kY0 = kEpi0 + kEpiB;
+  static constexpr int kScale0 = kY0 + kRows * kCols * m * 4;
+  static constexpr int kCode0 = kScale0 + kRows * kCols * 4;
+  static constexpr int kList0 = (kCode0 + kRows * kCols + 15) / 16 * 16;
+  static constexpr int kBytes = kList0 + kListB;
+  static_assert(kBytes <= kLdsBytes, "LDS budget");
+};
+
+// Producer: the separable Gaussian tables of a chunk (32 rows: 16 node
+// columns, then 16 node rows, x 64 points; zero past the chunk).
+template <typename T>
+__device__ __forceinline__ void gauss_tables(const LPParams& p, const float* raw, int kn,
+                                             float* tab, int pt, const float (&toff)[kTabIt],
+                                             float cxr, float cyr) {
+#pragma unroll
+  for (int it = 0; it < kTabIt; ++it) {
+    const int e = pt + it * kProd;
+    const int k = e & (KT - 1), row = e / KT;
+    float v = 0.0f;
+    if (k < kn) {
+      const float u = (row < kCols ? raw[k] - cxr : raw[RS + k] - cyr) * p.inv_h - toff[it];
+      v = __expf(-u * u) * (row < kCols ? WeightGain<T>::value : 1.0f);
+    }
+    tab[row * KSF + k] = v;
+  }
+}
+
+// Split two float32 values into `S` 16-bit terms each (each term the
+// rounding of what the earlier ones left), written as pairs at rows
+// dst + s * stride.
+template <int S, typename T>
+__device__ __forceinline__ void emit_terms(T* dst, size_t stride, float v0, float v1) {
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    uint32_t pr;
+    if (s + 1 < S) {
+      float r0, r1;
+      pr = pack2_rest<T>(v0, v1, r0, r1);
+      v0 = r0;
+      v1 = r1;
+    } else {
+      pr = pack2<T>(v0, v1);
+    }
+    *(uint32_t*)(dst + (size_t)s * stride) = pr;
+  }
+}
+
+// Monomials u_x^a u_y^b (a + b <= 2 DEG) of a point in the tile frame, in
+// mono_index order; zero for points beyond the reach of every node.
+template <int DEG>
+__device__ __forceinline__ void point_monomials(const LPParams& p, float x, float y, float cxr,
+                                                float cyr, float (&mo)[DEG == 1 ? 6 : 15]) {
+  const float ux = (x - cxr) * p.inv_h;
+  const float uy = (y - cyr) * p.inv_h;
+  const float one = (ux * ux + uy * uy <= p.cutoff2) ? 1.0f : 0.0f;
+  mo[0] = one;
+  mo[1] = one * ux;
+  mo[2] = one * uy;
+  mo[3] = mo[1] * ux;
+  mo[4] = mo[1] * uy;
+  mo[5] = mo[2] * uy;
+  if (DEG == 2) {
+    mo[6] = mo[3] * ux;
+    mo[7] = mo[3] * uy;
+    mo[8] = mo[4] * uy;
+    mo[9] = mo[5] * uy;
+    mo[10] = mo[6] * ux;
+    mo[11] = mo[6] * uy;
+    mo[12] = mo[7] * uy;
+    mo[13] = mo[8] * uy;
+    mo[14] = mo[9] * uy;
+  }
+}
+
+// Producer, pass 1: tables and the moment monomials (S1 terms, rows
+// s * 16 + j).  Pass 2: tables, the basis values u_x, u_y of the chunk's
+// points (float32, rows 1-2 of `bas`; zero past the reach), and the
+// attribute terms (rows s * kDs + d), zero past the reach: a point beyond
+// every node's reach then adds nothing whatever its effective weight, so
+// the matrix lanes need no reach mask of their own.
+// A thread owns two consecutive points and one eighth of the rows.
+template <int DEG, int NTV, int S1, typename T, bool PASS2>
+__device__ __forceinline__ void shape_chunk(const LPParams& p, const float* raw, int kn, int nv,
+                                            float* tab, float* bas, T* G, int pt,
+                                            const float (&toff)[kTabIt], float cxr,
+                                            float cyr) {
+  using L = ShapeLayout<DEG, NTV, S1>;
+  gauss_tables<T>(p, raw, kn, tab, pt, toff, cxr, cyr);
+  const int pp = pt & 31, g = pt >> 5;
+  const int k0 = 2 * pp;
+  float mo0[L::nmom], mo1[L::nmom];
+  point_monomials<DEG>(p, raw[k0], raw[RS + k0], cxr, cyr, mo0);
+  point_monomials<DEG>(p, raw[k0 + 1], raw[RS + k0 + 1], cxr, cyr, mo1);
+  if (!PASS2) {
+#pragma unroll
+    for (int j = 0; j < L::nmom; ++j)
+      if ((j & 7) == g)
+        emit_terms<S1, T>(G + (size_t)j * KSH + k0, (size_t)16 * KSH, mo0[j], mo1[j]);
+    return;
+  }
+#pragma unroll
+  for (int j = 1; j < 3; ++j)   // u_x, u_y (the matrix waves form the rest)
+    if ((j & 7) == g) {
+      bas[j * KSF + k0] = mo0[j];
+      bas[j * KSF + k0 + 1] = mo1[j];
+    }
+  const float* rv = raw + 2 * RS;
+  const float a0 = mo0[0] * AttrGain<T>::value, a1 = mo1[0] * AttrGain<T>::value;
+  for (int d = g; d < nv; d += 8)
+    emit_terms<kShapeS2, T>(G + (size_t)d * KSH + k0, (size_t)L::kDs * KSH, a0 * rv[d * RS + k0],
+                            a1 * rv[d * RS + k0 + 1]);
+}
+
+// The power of two that brings an effective weight's bound, `b`, to 2^14 ..
+// 2^15 (float16; at most 2^+-100), 1 for bfloat16.
+template <typename T>
+__device__ __forceinline__ float shape_scale(double b) {
+  if constexpr (__is_same(T, _Float16)) {
+    int e;
+    (void)frexp(b, &e);              // b < 2^e
+    e = 15 - e;
+    e = e > 100 ? 100 : (e < -100 ? -100 : e);
+    return b > 0.0 && b < __builtin_inf() ? ldexpf(1.0f, e) : 1.0f;
+  } else {
+    return 1.0f;
+  }
+}
+
+// One node tile and attribute slab: `block` indexes (slab, tile) as a launch's
+// workgroup index does.  Every thread of the workgroup calls it with the same
+// arguments.
+template <int DEG, int NTV, int S1, typename T>
+__device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* lds_sh) {
+  using L = ShapeLayout<DEG, NTV, S1>;
+  typedef typename Vec8<T>::type vec8;
+  constexpr int m = L::m;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool mma = wave < kMmaWaves;
+  const int pt = tid - kMmaWaves * 64;
+  const int slab = block / p.tiles;
+  const int tile = block % p.tiles;
+  const int c0 = (tile % p.tiles_x) * kCols;
+  const int r0 = (tile / p.tiles_x) * kRows;
+  const int d0 = slab * p.Ds;
+  const int nv = min(p.Ds, p.D - d0);
+  const float cxr = (float)(p.x0 + (double)(c0 + kCols / 2) * p.dx);
+  const float cyr = (float)(p.y0 + (double)(r0 + kRows / 2) * p.dy);
+
+  auto feat = [&](int b) { return (T*)(lds_sh + L::kFeat0 + b * L::kFeatB); };
+  auto tab = [&](int b) { return (float*)(lds_sh + L::kTab0 + b * L::kTabB); };
+  auto bas = [&](int b) { return (float*)(lds_sh + L::kBas0 + b * L::kBasB); };
+  auto raw = [&](int b) { return (float*)(lds_sh + L::kRaw0 + b * L::kRawB); };
+  float* epi = (float*)(lds_sh + L::kEpi0);
+  float* ybuf = (float*)(lds_sh + L::kY0);
+  float* back = (float*)(lds_sh + L::kScale0);
+  uint8_t* codes = (uint8_t*)(lds_sh + L::kCode0);
+
+  const int i = lane & 15;
+  const int k8 = (lane >> 4) * 8;
+  const int64_t plane = (int64_t)p.W * p.H;
+
+  // The points in reach, a list at a time; `kept` is the last list, which
+  // pass 2 uses again if it was the only one.
+  constexpr bool ADAPT = __is_same(T, __bf16);
+  const uint16_t* list = (const uint16_t*)(lds_sh + L::kList0);
+  const TileReach reach = tile_reach(p, c0, r0, cxr, cyr);
+  bool cut = ADAPT;   // the adaptive reach applies
+  float scale = __builtin_inff();
+  int kept = 0, segments = 0;
+  auto next_list = [&](int64_t& pos) {
+    return next_points<DEG, ADAPT>(p, reach, cut, pos, lds_sh + L::kList0, scale);
+  };
+  // rows of a chunk's 16-bit terms that are never written: zero in both buffers
+  auto zero_rows = [&](int rows, int stride, int terms, int t, int threads) {
+    for (int b = 0; b < 2; ++b)
+      for (int s = 0; s < terms; ++s) {
+        T* z = feat(b) + ((size_t)s * stride + rows) * KSH;
+        for (int e = t; e < (stride - rows) * KSH; e += threads) z[e] = (T)0.0f;
+      }
+  };
+  // producers: a chunk's loads, its tables and terms
+  const RowWalk rw1 = row_walk(pt, 0);
+  float toff[kTabIt];
+  auto make1 = [&](const Chunk& ch, int b) {
+    shape_chunk<DEG, NTV, S1, T, false>(p, raw(b), ch.kn, 0, tab(b), bas(b), feat(b), pt, toff,
+                                        cxr, cyr);
+  };
+  auto make2 = [&](const Chunk& ch, int b) {
+    shape_chunk<DEG, NTV, S1, T, true>(p, raw(b), ch.kn, nv, tab(b), bas(b), feat(b), pt, toff,
+                                       cxr, cyr);
+  };
+  // the first two raw chunks of a list at `base` to LDS, then chunk 0's tables
+  // and terms once the producers' stores are visible (`sync`)
+  auto load2 = [&](int64_t base, const Chunk& ch0, const Chunk& ch1) {
+    float ra[L::kRawIt], rb[L::kRawIt], xa = 0.0f, xb = 0.0f;
+    // (the walk's steps made here: held over pass 1 and its solve, they spill)
+    RowWalk rw2 = row_walk(pt, nv);
+    asm volatile("" : "+v"(rw2.k0), "+v"(rw2.d0));
+    raw_load_rows(p, ch0, base, list, d0, nv, rw2, pt, ra, xa);
+    raw_load_rows(p, ch1, base, list, d0, nv, rw2, pt, rb, xb);
+    raw_store_rows(raw(0), nv, rw2, pt, ra, xa);
+    raw_store_rows(raw(1), nv, rw2, pt, rb, xb);
+  };
+
+  // ---- pass 1: moments, then the ladder and the shape coefficients ----
+  // Once within the adaptive reach; once more without it where a node could
+  // see past it.
+  for (;;) {
+    zero_rows(L::nmom, 16, S1, tid, kThreads);
+    floatx4 acc[R];
+    // the first list, mostly the only one, by code that all waves share
+    // (their own copies of it would each come from the L2 once per tile)
+    int64_t base = 0, pos = 0;
+    kept = next_list(pos);
+    segments = 1;
+    if (mma) {
+#pragma unroll
+      for (int t = 0; t < R; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (;;) {
+        __syncthreads();   // raw 0 and 1
+        __syncthreads();   // chunk 0
+        Walker wk{0, kept};
+        int c = 0;
+        for (Chunk ch = walker_take(wk); ch.valid; ch = walker_take(wk), ++c) {
+          const float* gx = tab(c & 1);
+          const float* gy = tab(c & 1) + kCols * KSF;
+          const T* G = feat(c & 1);
+#pragma unroll
+          for (int ks = 0; ks < KT; ks += 32) {
+            float wx[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) wx[q] = gx[i * KSF + ks + k8 + q];
+            vec8 ahi[R], alo[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+              const float* gyr = gy + (wave * R + t) * KSF + ks + k8;
+              float w[8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) w[q] = wx[q] * gyr[q];
+              split_weights<T>(w, ahi[t], alo[t]);
+            }
+#pragma unroll
+            for (int s = 0; s < S1; ++s) {
+              const vec8 b = *(const vec8*)(G + ((size_t)s * 16 + i) * KSH + ks + k8);
+#pragma unroll
+              for (int t = 0; t < R; ++t) acc[t] = mfma16(ahi[t], b, acc[t]);
+              if (s + 1 < S1) {
+#pragma unroll
+                for (int t = 0; t < R; ++t) acc[t] = mfma16(alo[t], b, acc[t]);
+              }
+            }
+          }
+          __syncthreads();
+        }
+        if (pos >= p.n) break;
+        kept = next_list(pos);
+        ++segments;
+      }
+      // moments -> LDS [wave][node][monomial]
+      float* e = epi + wave * 16 * R * L::kEpiStride;
+#pragma unroll
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          e[(t * 16 + 4 * (lane >> 4) + r) * L::kEpiStride + (lane & 15)] = acc[t][r];
+    } else {
+      for (;;) {
+        Walker wk{0, kept};
+        Chunk ch0 = walker_take(wk);
+        Chunk ch1 = walker_take(wk);
+        float rr[1], rxy = 0.0f, rxy1 = 0.0f;   // coordinates only
+        raw_load_rows(p, ch0, base, list, d0, 0, rw1, pt, rr, rxy);
+        raw_load_rows(p, ch1, base, list, d0, 0, rw1, pt, rr, rxy1);
+        if (segments == 1) {   // loads in flight
+          int ptl = pt;
+          if (ADAPT) asm volatile("" : "+v"(ptl));
+          __builtin_assume(ptl >= 0 && ptl < kProd);
+          table_offsets(p, ptl, c0, r0, cxr, cyr, toff);
+        }
+        raw_store_rows(raw(0), 0, rw1, pt, rr, rxy);
+        raw_store_rows(raw(1), 0, rw1, pt, rr, rxy1);
+        __syncthreads();
+        if (ch0.valid) make1(ch0, 0);
+        __syncthreads();
+        for (int c = 0; ch0.valid; ++c) {
+          const Chunk ch2 = walker_take(wk);
+          raw_load_rows(p, ch2, base, list, d0, 0, rw1, pt, rr, rxy);
+          if (ch1.valid) make1(ch1, (c + 1) & 1);
+          raw_store_rows(raw(c & 1), 0, rw1, pt, rr, rxy);
+          __syncthreads();
+          ch0 = ch1;
+          ch1 = ch2;
+        }
+        if (pos >= p.n) break;
+        base = pos;
+        kept = next_list(pos);
+        ++segments;
+      }
+    }
+    __syncthreads();
+    // one node per lane on the first four waves (one per SIMD)
+    bool low = false;
+    if (tid < kRows * kCols) {
+      const int w = tid / (16 * R), local = tid % (16 * R);
+      const float* e = epi + (w * 16 * R + local) * L::kEpiStride;
+      const int t = local / 16, col = local % 16;
+      const int row = w * R + t;
+      const double ex = node_offset_xd(p, c0, col, cxr);
+      const double ey = node_offset_yd(p, r0, row, cyr);
+      Ladder<DEG> lad;
+      const int code = ladder_solve<DEG>(e, ex, ey, p.tau, p.floor_w,
+                                         (double)WeightGain<T>::value, lad);
+      const bool in = r0 + row < p.H && c0 + col < p.W;
+      low = ADAPT && in && code != 255 && lad.diag < (double)(scale * kDiagFloor);
+      float g = 1.0f;
+      if (__is_same(T, _Float16) && code != 255) {
+        double b = 0.0;   // z = S w in the node's frame, times the weights' gain
+#pragma unroll
+        for (int j = 0; j < m; ++j)
+          if (j < lad.mk) b += fabs(lad.s[j] * lad.w[j]);
+        g = shape_scale<T>(b * (double)WeightGain<T>::value);
+      }
+      float* yv = ybuf + (row * kCols + col) * m;
+#pragma unroll
+      for (int j = 0; j < m; ++j)
+        yv[j] = code == 255 ? 0.0f : (float)(lad.y[j] * (double)g);
+      back[row * kCols + col] = 1.0f / (g * AttrGain<T>::value);
+      codes[row * kCols + col] = (uint8_t)code;
+      if (p.deg_out && slab == 0 && in)
+        p.deg_out[(int64_t)(r0 + row) * p.W + c0 + col] = (uint8_t)code;
+    } else if (!mma && segments == 1) {
+      // the list is still there: pass 2's first chunks to LDS meanwhile
+      Walker wk{0, kept};
+      const Chunk ch0 = walker_take(wk), ch1 = walker_take(wk);
+      load2(0, ch0, ch1);
+    }
+    const bool redo = ADAPT && cut && __syncthreads_or(low);
+    if (!(ADAPT && cut)) __syncthreads();
+    if (!redo) break;
+    cut = false;
+  }
+
+  // ---- pass 2: effective weights x attribute terms ----
+  floatx4 acc[R][NTV];
+  int64_t base = 0, pos = segments == 1 ? p.n : 0;
+  if (segments > 1) kept = next_list(pos);
+  if (mma) {
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int q = 0; q < NTV; ++q) acc[t][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // the shape coefficients of this lane's nodes (column i of its strips)
+    float yv[R][m];
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int j = 0; j < m; ++j) yv[t][j] = ybuf[((wave * R + t) * kCols + i) * m + j];
+    for (;;) {
+      // (with one list its raw chunks 0 and 1 are in LDS)
+      if (segments > 1) __syncthreads();   // raw 0 and 1
+      __syncthreads();                     // chunk 0
+      Walker wk{0, kept};
+      int c = 0;
+      for (Chunk ch = walker_take(wk); ch.valid; ch = walker_take(wk), ++c) {
+        const float* gx = tab(c & 1);
+        const float* gy = tab(c & 1) + kCols * KSF;
+        const float* bs = bas(c & 1);
+        const T* G = feat(c & 1);
+#pragma unroll
+        for (int ks = 0; ks < KT; ks += 32) {
+          vec8 ahi[R], alo[R];
+          u32x4 hv[R], lv[R];
+          // two points at a time: their basis values and column factors,
+          // then the effective weight of each of the lane's nodes, split
+          // hi + lo with one packed conversion per pair
+#pragma unroll
+          for (int q = 0; q < 8; q += 2) {
+            float w[R][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int k = ks + k8 + q + e;
+              // b = (1, u_x, u_y[, u_x^2, u_x u_y, u_y^2]): the quadratic
+              // terms follow from the linear ones (Horner), so a point
+              // needs two values, not five (past the reach its attribute
+              // terms are zero)
+              const float b1 = bs[KSF + k], b2 = bs[2 * KSF + k];
+              const float wxq = gx[i * KSF + k];
+#pragma unroll
+              for (int t = 0; t < R; ++t) {
+                float sh;
+                if constexpr (DEG == 1) {
+                  sh = fmaf(yv[t][2], b2, fmaf(yv[t][1], b1, yv[t][0]));
+                } else {
+                  const float s1 = fmaf(yv[t][3], b1, fmaf(yv[t][4], b2, yv[t][1]));
+                  const float s2 = fmaf(yv[t][5], b2, yv[t][2]);
+                  sh = fmaf(b1, s1, fmaf(b2, s2, yv[t][0]));
+                }
+                w[t][e] = (wxq * gy[(wave * R + t) * KSF + k]) * sh;
+              }
+            }
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+              float r0, r1;
+              hv[t][q / 2] = pack2_rest<T>(w[t][0], w[t][1], r0, r1);
+              lv[t][q / 2] = pack2<T>(r0, r1);
+            }
+          }
+#pragma unroll
+          for (int t = 0; t < R; ++t) {
+            ahi[t] = __builtin_bit_cast(vec8, hv[t]);
+            alo[t] = __builtin_bit_cast(vec8, lv[t]);
+          }
+#pragma unroll
+          for (int q = 0; q < NTV; ++q) {
+            const vec8 b1 = *(const vec8*)(G + ((size_t)q * 16 + i) * KSH + ks + k8);
+            const vec8 b2 = *(const vec8*)(G + ((size_t)L::kDs + q * 16 + i) * KSH + ks + k8);
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+              acc[t][q] = mfma16(ahi[t], b1, acc[t][q]);
+              acc[t][q] = mfma16(alo[t], b1, acc[t][q]);
+              acc[t][q] = mfma16(ahi[t], b2, acc[t][q]);
+            }
+          }
+        }
+        __syncthreads();
+      }
+      if (pos >= p.n) break;
+      kept = next_list(pos);
+    }
+  } else {
+    zero_rows(nv, L::kDs, kShapeS2, pt, kProd);
+    const RowWalk rw2 = row_walk(pt, nv);
+    for (;;) {
+      Walker wk{0, kept};
+      Chunk ch0 = walker_take(wk);
+      Chunk ch1 = walker_take(wk);
+      if (segments > 1) {
+        load2(base, ch0, ch1);
+        __syncthreads();
+      }
+      if (ch0.valid) make2(ch0, 0);
+      __syncthreads();
+      float rr[L::kRawIt], rxy = 0.0f;
+      for (int c = 0; ch0.valid; ++c) {
+        const Chunk ch2 = walker_take(wk);
+        raw_load_rows(p, ch2, base, list, d0, nv, rw2, pt, rr, rxy);
+        if (ch1.valid) make2(ch1, (c + 1) & 1);
+        raw_store_rows(raw(c & 1), nv, rw2, pt, rr, rxy);
+        __syncthreads();
+        ch0 = ch1;
+        ch1 = ch2;
+      }
+      if (pos >= p.n) break;
+      base = pos;
+      kept = next_list(pos);
+    }
+  }
+  // fields: the accumulators are the normalised values times the node's
+  // scale; lane holds node columns 4 (lane / 16) + r of strip t for attribute
+  // q * 16 + lane % 16
+  if (mma) {
+#pragma unroll
+    for (int q = 0; q < NTV; ++q) {
+      const int dd = q * 16 + (lane & 15);
+      if (dd >= nv) continue;
+      const double sh = (double)p.shift[d0 + dd], sc = (double)p.scale[d0 + dd];
+      float* fd = p.fields + (int64_t)(d0 + dd) * plane;
+#pragma unroll
+      for (int t = 0; t < R; ++t) {
+        const int row = wave * R + t, rg = r0 + row;
+        if (rg >= p.H) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int col = 4 * (lane >> 4) + r, cg = c0 + col;
+          if (cg >= p.W) continue;
+          const int node = row * kCols + col;
+          const bool und = codes[node] == 255;
+          fd[(int64_t)rg * p.W + cg] =
+              und ? __builtin_nanf("")
+                  : (float)(sh + sc * ((double)acc[t][q][r] * (double)back[node]));
+        }
+      }
+    }
+  }
+}
+
+template <int DEG, int NTV, int S1, typename T>
+__global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
+  extern __shared__ __attribute__((aligned(16))) char lds_sh[];
+  shape_tile<DEG, NTV, S1, T>(p, blockIdx.x, lds_sh);
+}
+
+template <int DEG, int NTV, int S1, typename T>
+hipError_t launch_shape_impl(const LPParams& p, hipStream_t s) {
+  using L = ShapeLayout<DEG, NTV, S1>;
+  const size_t lds = (size_t)L::kBytes;
+  const void* fn = (const void*)fit_shape_kernel<DEG, NTV, S1, T>;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const int64_t blocks = (int64_t)p.tiles * p.nslab;
+  hipLaunchKernelGGL((fit_shape_kernel<DEG, NTV, S1, T>), dim3((unsigned)blocks), dim3(kThreads),
+                     lds, s, p);
+  return hipGetLastError();
+}
+
+template <int DEG, int S1, typename T>
+hipError_t launch_shape_ntv(const LPParams& p, int ntv, hipStream_t s) {
+  switch (ntv) {
+    case 1: return launch_shape_impl<DEG, 1, S1, T>(p, s);
+    case 2: return launch_shape_impl<DEG, 2, S1, T>(p, s);
+    case 3: return launch_shape_impl<DEG, 3, S1, T>(p, s);
+    default: return launch_shape_impl<DEG, 4, S1, T>(p, s);
+  }
+}
+
+template <int S1, typename T>
+hipError_t launch_shape_deg(const LPParams& p, int deg, int ntv, hipStream_t s) {
+  return deg == 1 ? launch_shape_ntv<1, S1, T>(p, ntv, s) : launch_shape_ntv<2, S1, T>(p, ntv, s);
+}
+
+template <typename T>
+hipError_t launch_shape_terms(const LPParams& p, int deg, int ntv, int terms, hipStream_t s) {
+  switch (terms) {
+    case 1: return launch_shape_deg<1, T>(p, deg, ntv, s);
+    case 2: return launch_shape_deg<2, T>(p, deg, ntv, s);
+    default: return launch_shape_deg<3, T>(p, deg, ntv, s);
+  }
 }
 
 // Persistent batch of served fits sharing one kernel shape: every
@@ -751,7 +1487,8 @@ __global__ __launch_bounds__(kThreads) void fit_lp_kernel(LPParams p) {
 // are loaded through the scalar cache as kernel arguments are, and the
 // work area is named as the dynamic LDS array itself, so that its accesses
 // are LDS instructions rather than flat ones.
-template <int DEG, int NTS, int S, typename T>
+// SHAPE: the two-pass form, NTS attribute tiles.
+template <int DEG, int NTS, int S, typename T, bool SHAPE>
 __device__ __noinline__ void lp_tile_item(const LPParams* __restrict__ pp, int block) {
   extern __shared__ __attribute__((aligned(16))) char lds_lp[];
   // the parameter block is written before the launch and only read by the
@@ -762,8 +1499,12 @@ __device__ __noinline__ void lp_tile_item(const LPParams* __restrict__ pp, int b
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
   typedef const __attribute__((address_space(4))) LPParams* ConstParams;
   const ConstParams pc = (ConstParams)(uintptr_t)(((uint64_t)hi << 32) | lo);
-  lp_tile<DEG, NTS, S, T, false, false>(*(const LPParams*)pc,
-                                        __builtin_amdgcn_readfirstlane(block), lds_lp);
+  if constexpr (SHAPE)
+    shape_tile<DEG, NTS, S, T>(*(const LPParams*)pc, __builtin_amdgcn_readfirstlane(block),
+                               lds_lp);
+  else
+    lp_tile<DEG, NTS, S, T, false, false>(*(const LPParams*)pc,
+                                          __builtin_amdgcn_readfirstlane(block), lds_lp);
 }
 
 // Thread 0 takes the next item in a branch at the top of the loop; it
@@ -774,7 +1515,7 @@ __device__ __noinline__ void lp_tile_item(const LPParams* __restrict__ pp, int b
 // last barrier straight to the first, and the loop it builds from that runs
 // their path until they leave it, which they never do: no item is taken
 // without thread 0.)
-template <int DEG, int NTS, int S, typename T>
+template <int DEG, int NTS, int S, typename T, bool SHAPE>
 __global__ __launch_bounds__(kThreads) void fit_lp_batch_kernel(LPBatch b) {
   __shared__ int sh_item, sh_skip;
   int cur_req = -1;       // request of the current run of items
@@ -823,510 +1564,11 @@ __global__ __launch_bounds__(kThreads) void fit_lp_batch_kernel(LPBatch b) {
     if (!skip) {
       // read in place (uniform, read-only): fields are loaded where used,
       // as kernel arguments are, instead of held in registers
-      lp_tile_item<DEG, NTS, S, T>(b.reqs + req, block);
+      lp_tile_item<DEG, NTS, S, T, SHAPE>(b.reqs + req, block);
     }
     ++cur_cnt;
     __syncthreads();
   }
-}
-
-// ---------------------------------------------------------------------------
-// Two-pass (shape-function) form of the same fit, for the bfloat16 path with
-// the Gaussian weight.  The field at node p is
-//   field_d(p) = y_p^T R_t,d = sum_i w_ip (y_p^T b_t(u_i)) f_i,d,
-// y_p = T'^T M_p'^{-1} e_0 the tile-frame coefficients of the node's shape
-// function (mls_solve.h).  Pass 1 contracts the weights with the moment
-// monomials only (one 16-column feature tile, S1 terms, split weight) and
-// solves every node's ladder for y_p; pass 2 streams the points again and
-// contracts the effective weights w_ip (y_p^T b_t(u_i)), formed per pair in
-// float32 and split hi + lo, with the attributes (two bfloat16 terms each).
-// The contraction width falls from n_mom + m D to n_mom + D (399 -> 79 for
-// the quadratic basis with 64 attributes); the solve runs once per node and
-// attribute slab instead of per feature.  The error stays the float32
-// accumulation of the moments in pass 1: the effective weights and the
-// attribute terms add about 2^-16 relative per pair, which is not amplified
-// by the conditioning (a numpy model of both forms gives the same error).
-// ---------------------------------------------------------------------------
-
-constexpr int kShapeDsCap = 64;    // attributes per workgroup slab
-constexpr int kShapeS2 = 2;        // bfloat16 terms per attribute value
-
-template <int DEG, int NTV, int S1>
-struct ShapeLayout {
-  static constexpr int m = DEG == 1 ? 3 : 6;
-  static constexpr int nmom = DEG == 1 ? 6 : 15;
-  static constexpr int kRows1 = S1 * 16;                 // pass 1 feature rows
-  static constexpr int kRows2 = kShapeS2 * NTV * 16;     // pass 2 feature rows
-  static constexpr int kFeatRows = kRows1 > kRows2 ? kRows1 : kRows2;
-  static constexpr int kDs = NTV * 16;
-  static constexpr int kRawFloats = (2 + kDs) * RS;
-  static constexpr int kRawIt = (kDs * KT + kProd - 1) / kProd;
-  static constexpr int kFeatB = kFeatRows * KSH * 2;
-  static constexpr int kTabB = (kCols + kRows) * KSF * 4;
-  static constexpr int kBasB = 3 * KSF * 4;              // 1, u_x, u_y per point
-  static constexpr int kRawB = kRawFloats * 4;
-  static constexpr int kFeat0 = 0;
-  static constexpr int kTab0 = kFeat0 + 2 * kFeatB;
-  static constexpr int kBas0 = kTab0 + 2 * kTabB;
-  static constexpr int kRaw0 = kBas0 + 2 * kBasB;
-  static constexpr int kLoop = kRaw0 + 2 * kRawB;
-  static constexpr int kEpiStride = 16 + 1;
-  static constexpr int kEpi = kMmaWaves * 16 * R * kEpiStride * 4;
-  static constexpr int kMain = kLoop > kEpi ? kLoop : kEpi;
-  // per node: the shape coefficients y (float32) and the degree code
-  static constexpr int kY0 = kMain;
-  static constexpr int kCode0 = kY0 + kRows * kCols * m * 4;
-  static constexpr int kList0 = (kCode0 + kRows * kCols + 15) / 16 * 16;
-  static constexpr int kBytes = kList0 + kListB;
-  static_assert(kBytes <= kLdsBytes, "LDS budget");
-};
-
-// Producer: the separable Gaussian tables of a chunk (32 rows: 16 node
-// columns, then 16 node rows, x 64 points; zero past the chunk).
-__device__ __forceinline__ void gauss_tables(const LPParams& p, const float* raw, int kn,
-                                             float* tab, int pt, const float (&toff)[kTabIt],
-                                             float cxr, float cyr) {
-#pragma unroll
-  for (int it = 0; it < kTabIt; ++it) {
-    const int e = pt + it * kProd;
-    const int k = e & (KT - 1), row = e / KT;
-    float v = 0.0f;
-    if (k < kn) {
-      const float u = (row < kCols ? raw[k] - cxr : raw[RS + k] - cyr) * p.inv_h - toff[it];
-      v = __expf(-u * u);
-    }
-    tab[row * KSF + k] = v;
-  }
-}
-
-// Split two float32 values into `S` bfloat16 terms each (each term the
-// rounding of what the earlier ones left), written as pairs at rows
-// dst + s * stride.
-template <int S>
-__device__ __forceinline__ void emit_terms(__bf16* dst, size_t stride, float v0, float v1) {
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    uint32_t pr;
-    if (s + 1 < S) {
-      float r0, r1;
-      pr = pack2_rest<__bf16>(v0, v1, r0, r1);
-      v0 = r0;
-      v1 = r1;
-    } else {
-      pr = pack2<__bf16>(v0, v1);
-    }
-    *(uint32_t*)(dst + (size_t)s * stride) = pr;
-  }
-}
-
-// Monomials u_x^a u_y^b (a + b <= 2 DEG) of a point in the tile frame, in
-// mono_index order; zero for points beyond the reach of every node.
-template <int DEG>
-__device__ __forceinline__ void point_monomials(const LPParams& p, float x, float y, float cxr,
-                                                float cyr, float (&mo)[DEG == 1 ? 6 : 15]) {
-  const float ux = (x - cxr) * p.inv_h;
-  const float uy = (y - cyr) * p.inv_h;
-  const float one = (ux * ux + uy * uy <= p.cutoff2) ? 1.0f : 0.0f;
-  mo[0] = one;
-  mo[1] = one * ux;
-  mo[2] = one * uy;
-  mo[3] = mo[1] * ux;
-  mo[4] = mo[1] * uy;
-  mo[5] = mo[2] * uy;
-  if (DEG == 2) {
-    mo[6] = mo[3] * ux;
-    mo[7] = mo[3] * uy;
-    mo[8] = mo[4] * uy;
-    mo[9] = mo[5] * uy;
-    mo[10] = mo[6] * ux;
-    mo[11] = mo[6] * uy;
-    mo[12] = mo[7] * uy;
-    mo[13] = mo[8] * uy;
-    mo[14] = mo[9] * uy;
-  }
-}
-
-// Producer, pass 1: tables and the moment monomials (S1 terms, rows
-// s * 16 + j).  Pass 2: tables, the basis values u_x, u_y of the chunk's
-// points (float32, rows 1-2 of `bas`; zero past the reach), and the
-// attribute terms (rows s * kDs + d), zero past the reach: a point beyond
-// every node's reach then adds nothing whatever its effective weight, so
-// the matrix lanes need no reach mask of their own.
-// A thread owns two consecutive points and one eighth of the rows.
-template <int DEG, int NTV, int S1, bool PASS2>
-__device__ __forceinline__ void shape_chunk(const LPParams& p, const float* raw, int kn, int nv,
-                                            float* tab, float* bas, __bf16* G, int pt,
-                                            const float (&toff)[kTabIt], float cxr,
-                                            float cyr) {
-  using L = ShapeLayout<DEG, NTV, S1>;
-  gauss_tables(p, raw, kn, tab, pt, toff, cxr, cyr);
-  const int pp = pt & 31, g = pt >> 5;
-  const int k0 = 2 * pp;
-  float mo0[L::nmom], mo1[L::nmom];
-  point_monomials<DEG>(p, raw[k0], raw[RS + k0], cxr, cyr, mo0);
-  point_monomials<DEG>(p, raw[k0 + 1], raw[RS + k0 + 1], cxr, cyr, mo1);
-  if (!PASS2) {
-#pragma unroll
-    for (int j = 0; j < L::nmom; ++j)
-      if ((j & 7) == g) emit_terms<S1>(G + (size_t)j * KSH + k0, (size_t)16 * KSH, mo0[j], mo1[j]);
-    return;
-  }
-#pragma unroll
-  for (int j = 1; j < 3; ++j)   // u_x, u_y (the matrix waves form the rest)
-    if ((j & 7) == g) {
-      bas[j * KSF + k0] = mo0[j];
-      bas[j * KSF + k0 + 1] = mo1[j];
-    }
-  const float* rv = raw + 2 * RS;
-  for (int d = g; d < nv; d += 8)
-    emit_terms<kShapeS2>(G + (size_t)d * KSH + k0, (size_t)L::kDs * KSH,
-                         mo0[0] * rv[d * RS + k0], mo1[0] * rv[d * RS + k0 + 1]);
-}
-
-template <int DEG, int NTV, int S1>
-__global__ __launch_bounds__(kThreads) void fit_shape_kernel(LPParams p) {
-  using L = ShapeLayout<DEG, NTV, S1>;
-  constexpr int m = L::m;
-  extern __shared__ __attribute__((aligned(16))) char lds_sh[];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool mma = wave < kMmaWaves;
-  const int pt = tid - kMmaWaves * 64;
-  const int slab = blockIdx.x / p.tiles;
-  const int tile = (int)(blockIdx.x % p.tiles);
-  const int c0 = (tile % p.tiles_x) * kCols;
-  const int r0 = (tile / p.tiles_x) * kRows;
-  const int d0 = slab * p.Ds;
-  const int nv = min(p.Ds, p.D - d0);
-  const float cxr = (float)(p.x0 + (double)(c0 + kCols / 2) * p.dx);
-  const float cyr = (float)(p.y0 + (double)(r0 + kRows / 2) * p.dy);
-
-  auto feat = [&](int b) { return (__bf16*)(lds_sh + L::kFeat0 + b * L::kFeatB); };
-  auto tab = [&](int b) { return (float*)(lds_sh + L::kTab0 + b * L::kTabB); };
-  auto bas = [&](int b) { return (float*)(lds_sh + L::kBas0 + b * L::kBasB); };
-  auto raw = [&](int b) { return (float*)(lds_sh + L::kRaw0 + b * L::kRawB); };
-  float* ybuf = (float*)(lds_sh + L::kY0);
-  uint8_t* codes = (uint8_t*)(lds_sh + L::kCode0);
-
-  const int i = lane & 15;
-  const int k8 = (lane >> 4) * 8;
-  const int64_t plane = (int64_t)p.W * p.H;
-
-  // The points in reach, a list at a time; `kept` is the last list, which
-  // pass 2 uses again if it was the only one.
-  const uint16_t* list = (const uint16_t*)(lds_sh + L::kList0);
-  const TileReach reach = tile_reach(p, c0, r0, cxr, cyr);
-  int kept = 0, segments = 0;
-  auto next_list = [&](int64_t& pos) {
-    return list_points<kThreads, kListCap>(
-        p.pts, p.n, pos, lds_sh + L::kList0,
-        [&](float x, float y) { return in_reach(reach, x, y); });
-  };
-
-  // ---- pass 1: moments, then the ladder and the shape coefficients ----
-  {
-    // feature rows past the moments are never written: zero them once
-    for (int b = 0; b < 2; ++b)
-      for (int s = 0; s < S1; ++s) {
-        __bf16* z = feat(b) + ((size_t)s * 16 + L::nmom) * KSH;
-        for (int e = tid; e < (16 - L::nmom) * KSH; e += kThreads) z[e] = (__bf16)0.0f;
-      }
-    floatx4 acc[R];
-    if (mma) {
-#pragma unroll
-      for (int t = 0; t < R; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-      for (int64_t pos = 0; pos < p.n; ++segments) {
-        kept = next_list(pos);
-        __syncthreads();   // raw 0 and 1
-        __syncthreads();   // chunk 0
-        Walker wk{0, kept};
-        int c = 0;
-        for (Chunk ch = walker_take(wk); ch.valid; ch = walker_take(wk), ++c) {
-          const float* gx = tab(c & 1);
-          const float* gy = tab(c & 1) + kCols * KSF;
-          const __bf16* G = feat(c & 1);
-#pragma unroll
-          for (int ks = 0; ks < KT; ks += 32) {
-            float wx[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) wx[q] = gx[i * KSF + ks + k8 + q];
-            bf16x8 ahi[R], alo[R];
-#pragma unroll
-            for (int t = 0; t < R; ++t) {
-              const float* gyr = gy + (wave * R + t) * KSF + ks + k8;
-              float w[8];
-#pragma unroll
-              for (int q = 0; q < 8; ++q) w[q] = wx[q] * gyr[q];
-              split_weights<__bf16>(w, ahi[t], alo[t]);
-            }
-#pragma unroll
-            for (int s = 0; s < S1; ++s) {
-              const bf16x8 b = *(const bf16x8*)(G + ((size_t)s * 16 + i) * KSH + ks + k8);
-#pragma unroll
-              for (int t = 0; t < R; ++t) acc[t] = mfma16(ahi[t], b, acc[t]);
-              if (s + 1 < S1) {
-#pragma unroll
-                for (int t = 0; t < R; ++t) acc[t] = mfma16(alo[t], b, acc[t]);
-              }
-            }
-          }
-          __syncthreads();
-        }
-      }
-    } else {
-      float toff[kTabIt];
-      table_offsets(p, pt, c0, r0, cxr, cyr, toff);
-      const RowWalk rw = row_walk(pt, 0);
-      for (int64_t pos = 0; pos < p.n; ++segments) {
-        const int64_t base = pos;
-        kept = next_list(pos);
-        Walker wk{0, kept};
-        Chunk ch0 = walker_take(wk);
-        Chunk ch1 = walker_take(wk);
-        float rr[1], rxy = 0.0f;   // coordinates only
-        auto load = [&](const Chunk& ch) {
-          raw_load_rows(p, ch, base, list, d0, 0, rw, pt, rr, rxy);
-        };
-        auto store = [&](int b) { raw_store_rows(raw(b), 0, rw, pt, rr, rxy); };
-        auto make = [&](const Chunk& ch, int b) {
-          shape_chunk<DEG, NTV, S1, false>(p, raw(b), ch.kn, 0, tab(b), bas(b), feat(b), pt, toff,
-                                           cxr, cyr);
-        };
-        load(ch0);
-        store(0);
-        load(ch1);
-        store(1);
-        __syncthreads();
-        if (ch0.valid) make(ch0, 0);
-        __syncthreads();
-        for (int c = 0; ch0.valid; ++c) {
-          const Chunk ch2 = walker_take(wk);
-          load(ch2);
-          if (ch1.valid) make(ch1, (c + 1) & 1);
-          store(c & 1);
-          __syncthreads();
-          ch0 = ch1;
-          ch1 = ch2;
-        }
-      }
-    }
-    // moments -> LDS [wave][node][monomial], then one node per lane: the
-    // ladder, the degree code and y (float32)
-    float* epi = (float*)lds_sh;
-    if (mma) {
-      float* e = epi + wave * 16 * R * L::kEpiStride;
-#pragma unroll
-      for (int t = 0; t < R; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          e[(t * 16 + 4 * (lane >> 4) + r) * L::kEpiStride + (lane & 15)] = acc[t][r];
-    }
-    __syncthreads();
-    // one node per lane on the first four waves (one per SIMD)
-    if (tid < kRows * kCols) {
-      const int w = tid / (16 * R), local = tid % (16 * R);
-      const float* e = epi + (w * 16 * R + local) * L::kEpiStride;
-      const int t = local / 16, col = local % 16;
-      const int row = w * R + t;
-      const double ex = node_offset_xd(p, c0, col, cxr);
-      const double ey = node_offset_yd(p, r0, row, cyr);
-      Ladder<DEG> lad;
-      const int code = ladder_solve<DEG>(e, ex, ey, p.tau, p.floor_w, 1.0, lad);
-      float* yv = ybuf + (row * kCols + col) * m;
-#pragma unroll
-      for (int j = 0; j < m; ++j) yv[j] = code == 255 ? 0.0f : (float)lad.y[j];
-      codes[row * kCols + col] = (uint8_t)code;
-      const int rr2 = r0 + row, cc = c0 + col;
-      if (p.deg_out && slab == 0 && rr2 < p.H && cc < p.W)
-        p.deg_out[(int64_t)rr2 * p.W + cc] = (uint8_t)code;
-    }
-    __syncthreads();
-  }
-
-  // ---- pass 2: effective weights x attribute terms ----
-  {
-    // attribute rows past this slab's values are never written: zero them
-    for (int b = 0; b < 2; ++b)
-      for (int s = 0; s < kShapeS2; ++s) {
-        __bf16* z = feat(b) + ((size_t)s * L::kDs + nv) * KSH;
-        for (int e = tid; e < (L::kDs - nv) * KSH; e += kThreads) z[e] = (__bf16)0.0f;
-      }
-    floatx4 acc[R][NTV];
-    if (mma) {
-#pragma unroll
-      for (int t = 0; t < R; ++t)
-#pragma unroll
-        for (int q = 0; q < NTV; ++q) acc[t][q] = floatx4{0.f, 0.f, 0.f, 0.f};
-      // the shape coefficients of this lane's nodes (column i of its strips)
-      float yv[R][m];
-#pragma unroll
-      for (int t = 0; t < R; ++t)
-#pragma unroll
-        for (int j = 0; j < m; ++j) yv[t][j] = ybuf[((wave * R + t) * kCols + i) * m + j];
-      for (int64_t pos = 0; pos < p.n;) {
-        if (segments == 1) pos = p.n;
-        else kept = next_list(pos);
-        __syncthreads();   // raw 0 and 1
-        __syncthreads();   // chunk 0
-        Walker wk{0, kept};
-        int c = 0;
-        for (Chunk ch = walker_take(wk); ch.valid; ch = walker_take(wk), ++c) {
-          const float* gx = tab(c & 1);
-          const float* gy = tab(c & 1) + kCols * KSF;
-          const float* bs = bas(c & 1);
-          const __bf16* G = feat(c & 1);
-#pragma unroll
-          for (int ks = 0; ks < KT; ks += 32) {
-            bf16x8 ahi[R], alo[R];
-            u32x4 hv[R], lv[R];
-            // two points at a time: their basis values and column factors,
-            // then the effective weight of each of the lane's nodes, split
-            // hi + lo with one packed conversion per pair
-#pragma unroll
-            for (int q = 0; q < 8; q += 2) {
-              float w[R][2];
-#pragma unroll
-              for (int e = 0; e < 2; ++e) {
-                const int k = ks + k8 + q + e;
-                // b = (1, u_x, u_y[, u_x^2, u_x u_y, u_y^2]): the quadratic
-                // terms follow from the linear ones (Horner), so a point
-                // needs two values, not five (past the reach its attribute
-                // terms are zero)
-                const float b1 = bs[KSF + k], b2 = bs[2 * KSF + k];
-                const float wxq = gx[i * KSF + k];
-#pragma unroll
-                for (int t = 0; t < R; ++t) {
-                  float sh;
-                  if (DEG == 1) {
-                    sh = fmaf(yv[t][2], b2, fmaf(yv[t][1], b1, yv[t][0]));
-                  } else {
-                    const float s1 = fmaf(yv[t][3], b1, fmaf(yv[t][4], b2, yv[t][1]));
-                    const float s2 = fmaf(yv[t][5], b2, yv[t][2]);
-                    sh = fmaf(b1, s1, fmaf(b2, s2, yv[t][0]));
-                  }
-                  w[t][e] = (wxq * gy[(wave * R + t) * KSF + k]) * sh;
-                }
-              }
-#pragma unroll
-              for (int t = 0; t < R; ++t) {
-                float r0, r1;
-                hv[t][q / 2] = pack2_rest<__bf16>(w[t][0], w[t][1], r0, r1);
-                lv[t][q / 2] = pack2<__bf16>(r0, r1);
-              }
-            }
-#pragma unroll
-            for (int t = 0; t < R; ++t) {
-              ahi[t] = __builtin_bit_cast(bf16x8, hv[t]);
-              alo[t] = __builtin_bit_cast(bf16x8, lv[t]);
-            }
-#pragma unroll
-            for (int q = 0; q < NTV; ++q) {
-              const bf16x8 b1 = *(const bf16x8*)(G + ((size_t)q * 16 + i) * KSH + ks + k8);
-              const bf16x8 b2 =
-                  *(const bf16x8*)(G + ((size_t)L::kDs + q * 16 + i) * KSH + ks + k8);
-#pragma unroll
-              for (int t = 0; t < R; ++t) {
-                acc[t][q] = mfma16(ahi[t], b1, acc[t][q]);
-                acc[t][q] = mfma16(alo[t], b1, acc[t][q]);
-                acc[t][q] = mfma16(ahi[t], b2, acc[t][q]);
-              }
-            }
-          }
-          __syncthreads();
-        }
-      }
-    } else {
-      float toff[kTabIt];
-      table_offsets(p, pt, c0, r0, cxr, cyr, toff);
-      const RowWalk rw = row_walk(pt, nv);
-      for (int64_t pos = 0; pos < p.n;) {
-        const int64_t base = pos;
-        if (segments == 1) pos = p.n;
-        else kept = next_list(pos);
-        Walker wk{0, kept};
-        Chunk ch0 = walker_take(wk);
-        Chunk ch1 = walker_take(wk);
-        float rr[L::kRawIt], rxy = 0.0f;
-        auto load = [&](const Chunk& ch) {
-          raw_load_rows(p, ch, base, list, d0, nv, rw, pt, rr, rxy);
-        };
-        auto store = [&](int b) { raw_store_rows(raw(b), nv, rw, pt, rr, rxy); };
-        auto make = [&](const Chunk& ch, int b) {
-          shape_chunk<DEG, NTV, S1, true>(p, raw(b), ch.kn, nv, tab(b), bas(b), feat(b), pt, toff,
-                                          cxr, cyr);
-        };
-        load(ch0);
-        store(0);
-        load(ch1);
-        store(1);
-        __syncthreads();
-        if (ch0.valid) make(ch0, 0);
-        __syncthreads();
-        for (int c = 0; ch0.valid; ++c) {
-          const Chunk ch2 = walker_take(wk);
-          load(ch2);
-          if (ch1.valid) make(ch1, (c + 1) & 1);
-          store(c & 1);
-          __syncthreads();
-          ch0 = ch1;
-          ch1 = ch2;
-        }
-      }
-    }
-    // fields: the accumulators are the normalised values; lane holds node
-    // columns 4 (lane / 16) + r of strip t for attribute q * 16 + lane % 16
-    if (mma) {
-#pragma unroll
-      for (int q = 0; q < NTV; ++q) {
-        const int dd = q * 16 + (lane & 15);
-        if (dd >= nv) continue;
-        const double sh = (double)p.shift[d0 + dd], sc = (double)p.scale[d0 + dd];
-        float* fd = p.fields + (int64_t)(d0 + dd) * plane;
-#pragma unroll
-        for (int t = 0; t < R; ++t) {
-          const int row = wave * R + t, rg = r0 + row;
-          if (rg >= p.H) continue;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int col = 4 * (lane >> 4) + r, cg = c0 + col;
-            if (cg >= p.W) continue;
-            const bool und = codes[row * kCols + col] == 255;
-            fd[(int64_t)rg * p.W + cg] =
-                und ? __builtin_nanf("") : (float)(sh + sc * (double)acc[t][q][r]);
-          }
-        }
-      }
-    }
-  }
-}
-
-template <int DEG, int NTV, int S1>
-hipError_t launch_shape_impl(const LPParams& p, hipStream_t s) {
-  using L = ShapeLayout<DEG, NTV, S1>;
-  const size_t lds = (size_t)L::kBytes;
-  const void* fn = (const void*)fit_shape_kernel<DEG, NTV, S1>;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  const int64_t blocks = (int64_t)p.tiles * p.nslab;
-  hipLaunchKernelGGL((fit_shape_kernel<DEG, NTV, S1>), dim3((unsigned)blocks), dim3(kThreads), lds,
-                     s, p);
-  return hipGetLastError();
-}
-
-template <int DEG, int S1>
-hipError_t launch_shape_ntv(const LPParams& p, int ntv, hipStream_t s) {
-  switch (ntv) {
-    case 1: return launch_shape_impl<DEG, 1, S1>(p, s);
-    case 2: return launch_shape_impl<DEG, 2, S1>(p, s);
-    case 3: return launch_shape_impl<DEG, 3, S1>(p, s);
-    default: return launch_shape_impl<DEG, 4, S1>(p, s);
-  }
-}
-
-template <int S1>
-hipError_t launch_shape_deg(const LPParams& p, int deg, int ntv, hipStream_t s) {
-  return deg == 1 ? launch_shape_ntv<1, S1>(p, ntv, s) : launch_shape_ntv<2, S1>(p, ntv, s);
 }
 
 template <int DEG, int NTS, int S, typename T, bool WEND>
@@ -1377,11 +1619,12 @@ hipError_t launch_lp_terms(const LPParams& p, int deg, int nts, int terms, hipSt
 
 // One workgroup per resident slot of the device (compute units x the
 // kernel's occupancy), at most one per item, at most max_grid if nonzero.
-template <int DEG, int NTS, int S, typename T>
+template <int DEG, int NTS, int S, typename T, bool SHAPE>
 hipError_t launch_batch_impl(const LPBatch& b, int max_grid, hipStream_t s) {
-  using L = LPLayout<DEG, NTS, S, T>;
-  const size_t lds = (size_t)L::kBytes;
-  const void* fn = (const void*)fit_lp_batch_kernel<DEG, NTS, S, T>;
+  size_t lds;
+  if constexpr (SHAPE) lds = (size_t)ShapeLayout<DEG, NTS, S>::kBytes;
+  else lds = (size_t)LPLayout<DEG, NTS, S, T>::kBytes;
+  const void* fn = (const void*)fit_lp_batch_kernel<DEG, NTS, S, T, SHAPE>;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int dev = 0, cus = 0, per_cu = 0;
@@ -1395,23 +1638,35 @@ hipError_t launch_batch_impl(const LPBatch& b, int max_grid, hipStream_t s) {
   if (grid > b.n_items) grid = b.n_items;
   if (max_grid > 0 && grid > max_grid) grid = max_grid;
   if (grid < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fit_lp_batch_kernel<DEG, NTS, S, T>), dim3((unsigned)grid), dim3(kThreads),
-                     lds, s, b);
+  hipLaunchKernelGGL((fit_lp_batch_kernel<DEG, NTS, S, T, SHAPE>), dim3((unsigned)grid),
+                     dim3(kThreads), lds, s, b);
   return hipGetLastError();
 }
 
 template <int DEG, int S, typename T>
 hipError_t launch_batch_nts(const LPBatch& b, int nts, int grid, hipStream_t s) {
   switch (nts) {
-    case 1: return launch_batch_impl<DEG, 1, S, T>(b, grid, s);
-    case 2: return launch_batch_impl<DEG, 2, S, T>(b, grid, s);
-    case 3: return launch_batch_impl<DEG, 3, S, T>(b, grid, s);
-    case 4: return launch_batch_impl<DEG, 4, S, T>(b, grid, s);
-    case 5: return launch_batch_impl<DEG, 5, S, T>(b, grid, s);
-    case 6: return launch_batch_impl<DEG, 6, S, T>(b, grid, s);
-    case 7: return launch_batch_impl<DEG, 7, S, T>(b, grid, s);
-    default: return launch_batch_impl<DEG, 8, S, T>(b, grid, s);
+    case 1: return launch_batch_impl<DEG, 1, S, T, false>(b, grid, s);
+    case 2: return launch_batch_impl<DEG, 2, S, T, false>(b, grid, s);
+    case 3: return launch_batch_impl<DEG, 3, S, T, false>(b, grid, s);
+    case 4: return launch_batch_impl<DEG, 4, S, T, false>(b, grid, s);
+    case 5: return launch_batch_impl<DEG, 5, S, T, false>(b, grid, s);
+    case 6: return launch_batch_impl<DEG, 6, S, T, false>(b, grid, s);
+    case 7: return launch_batch_impl<DEG, 7, S, T, false>(b, grid, s);
+    case 8: return launch_batch_impl<DEG, 8, S, T, false>(b, grid, s);
+    default: break;
   }
+  if constexpr (DEG > 0) {
+    // the two-pass form, kBatchShape + its attribute tiles
+    switch (nts - kBatchShape) {
+      case 1: return launch_batch_impl<DEG, 1, S, T, true>(b, grid, s);
+      case 2: return launch_batch_impl<DEG, 2, S, T, true>(b, grid, s);
+      case 3: return launch_batch_impl<DEG, 3, S, T, true>(b, grid, s);
+      case 4: return launch_batch_impl<DEG, 4, S, T, true>(b, grid, s);
+      default: break;
+    }
+  }
+  return hipErrorInvalidValue;
 }
 
 template <int S, typename T>

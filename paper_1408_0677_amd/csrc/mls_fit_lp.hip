@@ -56,6 +56,13 @@ void lp_slab_plan(int degree, int D, int forced_ds, int* nts_out, int* ds_out, i
   *nslab_out = best_ns;
 }
 
+// Slabs of the two-pass form: attribute tiles of 16, attributes per slab.
+static void shape_slab_plan(int D, int* ntv, int* ds, int* nslab) {
+  *nslab = (D + kShapeDsCap - 1) / kShapeDsCap;
+  *ds = (D + *nslab - 1) / *nslab;
+  *ntv = (*ds + 15) / 16;
+}
+
 // ---- served batches ----
 
 bool lp_batch_class(const FitArgs& a, bool fp16, int terms, LPBatchClass* cls) {
@@ -109,6 +116,7 @@ static LPParams dense_lp_params(const FitArgs& a, const float* vals_s, const flo
   // rounds to zero in both of its terms; 27.8 leaves 0.07 for the float32
   // exponent.  bfloat16 has float32's range: only the anchor test applies.
   p.reach2 = fp16 ? 27.8f : __builtin_inff();
+  p.list_log = (float)(log((double)a.n) + 36.0 * 0.6931471805599453);
   p.fields = a.fields;
   p.deg_out = a.deg_out;
   p.grads = nullptr;
@@ -120,7 +128,10 @@ static LPParams dense_lp_params(const FitArgs& a, const float* vals_s, const flo
 
 void lp_params_write(const FitArgs& a, const float* vals_s, const float* shift,
                      const float* scale, bool fp16, void* out) {
-  const LPParams p = dense_lp_params(a, vals_s, shift, scale, fp16);
+  LPParams p = dense_lp_params(a, vals_s, shift, scale, fp16);
+  int ntv;
+  if (lp_use_shape_form(a.degree, a.D, fp16, a.wkind, false, fp16 ? 2 : 3, 0, a.lp_form))
+    shape_slab_plan(a.D, &ntv, &p.Ds, &p.nslab);
   memcpy(out, &p, sizeof(p));
 }
 
@@ -139,7 +150,8 @@ hipError_t launch_fit_lp_batch(const LPBatchClass& c, const void* d_params, cons
   b.cancel = h_cancel;
   b.n_items = n_items;
   if (c.terms != (c.fp16 ? 2 : 3)) return hipErrorInvalidValue;
-  return launch_lp_batch(b, c.fp16, c.deg, c.nts, grid, s);
+  return c.fp16 ? launch_batch_fp16(b, c.deg, c.nts, grid, s)
+                : launch_batch_bf16(b, c.deg, c.nts, grid, s);
 }
 
 // Largest node offset across a tile, in units of h.
@@ -172,10 +184,10 @@ hipError_t launch_fit_lp(const FitArgs& a, const float* vals_s, const float* shi
   if (lp_use_shape_form(a.degree, a.D, fp16, a.wkind, a.grads != nullptr, terms, 0,
                         a.lp_form)) {
     LPParams p = dense_lp_params(a, vals_s, shift, scale, fp16);
-    p.nslab = (a.D + kShapeDsCap - 1) / kShapeDsCap;
-    p.Ds = (a.D + p.nslab - 1) / p.nslab;
-    const int ntv = (p.Ds + 15) / 16;
-    return launch_lp_shape(p, a.degree, ntv, terms, stream);
+    int ntv;
+    shape_slab_plan(a.D, &ntv, &p.Ds, &p.nslab);
+    return fp16 ? launch_shape_fp16(p, a.degree, ntv, terms, stream)
+                : launch_shape_bf16(p, a.degree, ntv, terms, stream);
   }
   // the same parameters a served batch passes for the request, so that a
   // request computes the same bits alone and in a batch

@@ -71,17 +71,17 @@ mls_status_t fit_prepare_c(void* ctx, const float* d_points, const float* d_valu
 // size.  The served batches stage their requests there.
 void* context_scratch(void* ctx, size_t* bytes);
 
-// Served batches of one-pass 16-bit fits with the Gaussian weight: requests
-// of one class (degree, feature tiles per slab, terms, float16 or bfloat16)
+// Served batches of 16-bit fits with the Gaussian weight: requests of one
+// class (degree, form, tiles per slab, terms, float16 or bfloat16)
 // share a persistent kernel that takes (request, block) items from a device
 // counter (mls_server.cpp).
 struct LPBatchClass {
-  int deg, nts, terms;
+  int deg, nts, terms;   // nts: feature tiles, or 8 + attribute tiles (two passes)
   bool fp16;
   int64_t blocks;        // work items of this request (tiles x slabs)
 };
-// False if the request does not run the one-pass Gaussian kernel with its
-// format's default term count (3 bfloat16, 2 float16 terms).
+// False if the request does not run a Gaussian kernel without slopes and with
+// its format's default term count (3 bfloat16, 2 float16 terms).
 bool lp_batch_class(const FitArgs& a, bool fp16, int terms, LPBatchClass* cls);
 // The kernel parameters of one request (lp_params_bytes() bytes, opaque).
 size_t lp_params_bytes();

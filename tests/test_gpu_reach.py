@@ -194,3 +194,44 @@ def test_not_finite(torch_dev, prec, d):
     inf[-1] = [np.inf, 0.0]
     F2, d2 = gpu_fit(torch_dev, inf, np.vstack([vals, vals[:1]]), grid, **kw)
     assert (d2 == 0).all() and np.isnan(F2).all()
+
+
+@pytest.mark.parametrize("basis,d", [("linear", 2), ("quadratic", 2), ("linear", 33),
+                                     ("quadratic", 20)])
+def test_bf16_moments_from_beyond_reach(torch_dev, oracle, basis, d):
+    """Nodes exactly on a point and on their tile's anchor, whose neighbours
+    are 6 h away and more: their first moments come from weights of e^-36 and
+    less, below what the sums over the reach resolve, and the tile is summed
+    again over all points."""
+    note(f"case bf16 beyond reach {basis} d={d}")
+    h = 1.0 / 64
+    dx = h / 8
+    c, r = 8 + 48 * np.arange(3), 8 + 48 * np.arange(3)
+    pts = (np.stack(np.meshgrid(c, r), -1).reshape(-1, 2) * dx).astype(np.float32)
+    vals = np.random.default_rng(4).random((pts.shape[0], d)).astype(np.float32)
+    grid = {"x0": 0.0, "y0": 0.0, "dx": dx, "dy": dx, "width": 112, "height": 112}
+    kw = dict(basis=basis, h=h)
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, precision="bf16", **kw)
+    of, od, dm = oracle.fit_grid(pts, vals, grid, **kw)
+    on = (r[:, None] * 112 + c[None, :]).ravel()
+    assert (od.ravel()[on] > 0).all() and np.array_equal(deg[on], od.ravel()[on])
+    assert np.abs(F[:, on] - vals.T).max() <= 2e-3 * np.ptp(vals)
+    # (between the points one of them is all that a node sees in float32: the
+    # degrees there are its rounding's, the fields are not)
+    st = compare(F, deg, of.reshape(d, -1), od.ravel(), dm.ravel(), vals, dmin_pass=1e-2)
+    assert st["nan_ok"] and st["max_err_pass"] <= 2e-3 and st["rms_err_pass"] <= 1e-4, st
+
+
+@pytest.mark.parametrize("n", [40, 5000])
+def test_bf16_zero_floor_far_from_the_points(torch_dev, n):
+    """With a weight floor of 0 nodes 8 h from every point are determined by
+    weights of e^-64 alone, which no sum of weights bounds from below."""
+    note(f"case bf16 zero floor n={n}")
+    rng = np.random.default_rng(n)
+    pts = (rng.random((n, 2)) * 0.05).astype(np.float32)
+    vals = rng.random((n, 3)).astype(np.float32)
+    grid = {"x0": 0.39, "y0": 0.0, "dx": 0.004, "dy": 0.004, "width": 16, "height": 16}
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, basis="constant", h=0.05, weight_floor=0.0,
+                     precision="bf16")
+    assert (deg == 0).any() and np.isfinite(F[:, deg == 0]).all()
+    assert F[:, deg == 0].min() >= -0.01 and F[:, deg == 0].max() <= 1.01
