@@ -126,7 +126,7 @@ typedef struct {
                            slab, 0 = the library's plan, else 1 ..
                            MLS_LP_MAX_SLAB_<basis>.  A tuning knob only:
                            results are bitwise the same for every value */
-  int32_t lp_form;      /* MLS_PREC_BF16 with the Gaussian weight, linear or
+  int32_t lp_form;      /* MLS_PREC_BF16/FP16, Gaussian weight, linear or
                            quadratic basis, no gradients: 0 = the library's
                            choice, 1 = one pass (moments and right-hand
                            sides together, F = n_mom + m D columns),

@@ -69,9 +69,13 @@ bool lp_batch_class(const FitArgs& a, bool fp16, int terms, LPBatchClass* cls) {
   if (a.wkind != 0 || a.grads || a.rigid) return false;
   // batch kernels exist for each format's default term count
   if (terms != (fp16 ? 2 : 3)) return false;
-  if (lp_use_shape_form(a.degree, a.D, fp16, a.wkind, false, terms, 0, a.lp_form)) return false;
   int nts, ds, nslab;
-  lp_slab_plan(a.degree, a.D, a.lp_slab, &nts, &ds, &nslab);
+  if (lp_use_shape_form(a.degree, a.D, fp16, a.wkind, false, terms, 0, a.lp_form)) {
+    shape_slab_plan(a.D, &nts, &ds, &nslab);
+    nts += kBatchShape;
+  } else {
+    lp_slab_plan(a.degree, a.D, a.lp_slab, &nts, &ds, &nslab);
+  }
   cls->deg = a.degree;
   cls->nts = nts;
   cls->terms = terms;
@@ -162,18 +166,26 @@ double lp_tile_extent(double dx, double dy, double h) {
 
 bool lp_use_shape_form(int degree, int D, bool fp16, int wkind, bool grads, int terms,
                        int forced_ds, int form) {
-  if (fp16 || wkind != 0 || grads || degree < 1) return false;
+  if (wkind != 0 || grads || degree < 1) return false;
   if (form == 1) return false;
   if (form == 2) return true;
-  // the library's choice: the two-pass form once the one-pass form would
-  // issue at least twice its matrix instructions
+  // The library's choice.  Two passes list once and contract twice; each has
+  // a chunk's weights, tables and barrier, so fewer matrix instructions alone
+  // do not pay.  float16 (7,351 points, 701 x 643, us one pass / two): one slab
+  // either way, quadratic d = 5 346 / 491, linear d = 33 465 / 592; two slabs
+  // in one pass, quadratic d = 19 687 / 554, linear d = 48 729 / 621, d = 64
+  // 869 / 709: two passes where they need fewer slabs.  bfloat16, whose third
+  // term costs one pass more, also where one pass issues 2.4 times the matrix
+  // instructions: linear d = 19 (2.27 times) 522 / 617, d = 33 (2.5) 741 / 707,
+  // quadratic d = 15, 3,000 points (4.4) 456 / 353.
   int nts, ds, nslab;
   lp_slab_plan(degree, D, forced_ds, &nts, &ds, &nslab);
-  const int one = nslab * nts * (2 * terms - 1);
   const int nslab2 = (D + kShapeDsCap - 1) / kShapeDsCap;
+  if (fp16) return nslab > nslab2;
+  const int one = nslab * nts * (2 * terms - 1);
   const int per2 = (D + nslab2 - 1) / nslab2;
   const int two = nslab2 * ((2 * terms - 1) + 3 * ((per2 + 15) / 16));
-  return one >= 2 * two;
+  return 5 * one >= 12 * two;
 }
 
 hipError_t launch_fit_lp(const FitArgs& a, const float* vals_s, const float* shift,

@@ -196,6 +196,63 @@ def test_not_finite(torch_dev, prec, d):
     assert (d2 == 0).all() and np.isnan(F2).all()
 
 
+# attributes: one and two attribute tiles and slabs of the two-pass form, and
+# either side of where float16 needs a second slab in one pass
+@pytest.mark.parametrize("n", [63, 65, 1500, 5003])
+@pytest.mark.parametrize("basis,d", [("linear", 1), ("linear", 40), ("linear", 41), ("linear", 65),
+                                     ("quadratic", 15), ("quadratic", 17), ("quadratic", 64),
+                                     ("quadratic", 100)])
+def test_fp16_two_pass_form(torch_dev, oracle, basis, d, n):
+    """The float16 form in two passes at list, chunk and attribute edges, with
+    fields of very different sizes: against the oracle, and its nodes' degrees
+    against those of the one-pass form (the same moments)."""
+    from paper_1408_0677_amd import workloads as wl
+    note(f"case fp16 two pass {basis} n={n} d={d}")
+    rng = np.random.default_rng(n + d)
+    pts = wl.uniform_points(rng, n).astype(np.float32)
+    size = np.float32(10.0) ** (np.arange(d) % 7 - 3).astype(np.float32)
+    vals = (wl.smooth_fields(rng, pts, d) * size).astype(np.float32)
+    h = 1.2 / np.sqrt(n) + 0.03
+    dx = h / 20.0
+    grid = {"x0": 0.31, "y0": 0.42, "dx": dx, "dy": dx, "width": 37, "height": 19}
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, basis=basis, h=h, precision="fp16", lp_form=2)
+    of, od, dm = oracle.fit_grid(pts, vals, grid, basis=basis, h=h)
+    check("fp16", F, deg, of.reshape(d, -1), od.ravel(), dm.ravel(), vals)
+    _, one = gpu_fit(torch_dev, pts, vals, grid, basis=basis, h=h, precision="fp16", lp_form=1)
+    assert (deg != one).mean() <= 0.03
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("d", [19, 70])
+def test_two_pass_requests_in_a_batch(torch_dev, prec, d):
+    """Two-pass requests share a persistent kernel; each computes the bits that
+    it computes alone."""
+    from paper_1408_0677_amd import api, workloads as wl
+    note(f"case two pass batch {prec} d={d}")
+    rng = np.random.default_rng(d)
+    srv = api.Server(slots=1, hbm_budget=1 << 30, slot_scratch=64 << 20)
+    subs = []
+    for q, n in enumerate([200, 3001, 4200, 900, 2500, 64]):
+        pts = wl.uniform_points(rng, n).astype(np.float32)
+        P = torch_dev.from_numpy(pts).cuda()
+        V = torch_dev.from_numpy(wl.smooth_fields(rng, pts, d).astype(np.float32)).cuda()
+        grid = {"x0": 0.1, "y0": 0.1, "dx": 0.004, "dy": 0.004, "width": 60 + q, "height": 33 + q}
+        kw = dict(basis="quadratic" if q % 2 else "linear", h=0.05 + 2.0 / np.sqrt(n),
+                  precision=prec)
+        out = torch_dev.empty((d, grid["height"], grid["width"]), device="cuda")
+        deg = torch_dev.empty((grid["height"], grid["width"]), dtype=torch_dev.uint8,
+                              device="cuda")
+        subs.append((srv.submit(srv.put_points(P, V), grid, out, deg, **kw), P, V, grid, kw, out,
+                     deg))
+    for t, *_ in subs:
+        assert srv.wait(t)["status"] == 0
+    for _, P, V, grid, kw, out, deg in subs:
+        F, D = api.fit(P, V, grid, **kw)
+        assert torch_dev.equal(F.view(torch_dev.int32), out.view(torch_dev.int32))
+        assert torch_dev.equal(D, deg)
+    srv.close()
+
+
 @pytest.mark.parametrize("basis,d", [("linear", 2), ("quadratic", 2), ("linear", 33),
                                      ("quadratic", 20)])
 def test_bf16_moments_from_beyond_reach(torch_dev, oracle, basis, d):
