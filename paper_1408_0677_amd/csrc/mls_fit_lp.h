@@ -53,11 +53,12 @@
 // list_adaptive).  The test costs a point 8 bytes of L2 and a few
 // instructions per tile, against about 2 us of a compute unit per 64 points
 // contracted.  50,000 points, 64 attributes, h = 0.015, 2048^2 (bfloat16, two
-// passes): 206.3 ms over all points, 14.2 within 8 h (39 chunks a pass), 9.6
-// within the adaptive reach (25).  There a tile takes 350,000 cycles: 42,000
-// of listing, 87,000 of pass 1, 13,000 of solves, 185,000 of pass 2, 18,000 of
-// stores; in pass 2 the vector instructions of the effective weights and the
-// producers bound it, the matrix instructions are a fifth.
+// passes): 206.3 ms over all points, 14.2 within 8 h (39 chunks a pass), 9.5
+// within the adaptive reach (25), 7.8 with attributes loaded by 16 bytes.
+// There a tile takes 290,000 cycles: 42,000 of listing, 87,000 of pass 1,
+// 13,000 of solves, about 125,000 of pass 2, 18,000 of stores; in pass 2 the
+// vector instructions of the effective weights and the producers bound it, the
+// matrix instructions are a quarter.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -915,8 +916,13 @@ struct ShapeLayout {
   static constexpr int kRows2 = kShapeS2 * NTV * 16;     // pass 2 feature rows
   static constexpr int kFeatRows = kRows1 > kRows2 ? kRows1 : kRows2;
   static constexpr int kDs = NTV * 16;
-  static constexpr int kRawFloats = (2 + kDs) * RS;
-  static constexpr int kRawIt = (kDs * KT + kProd - 1) / kProd;
+  // a raw chunk: coordinates (2 rows of KT), then kDs attributes per point,
+  // 16 bytes more a point so that eight lanes' 16 bytes of consecutive points
+  // lie in different banks
+  static constexpr int kRawRows = 2 * RS + 2;
+  static constexpr int kRawStride = kDs + 4;
+  static constexpr int kRawFloats = kRawRows + KT * kRawStride;
+  static constexpr int kRawIt = kDs / 4 * KT / kProd;    // 16-byte loads a thread
   static constexpr int kFeatB = kFeatRows * KSH * 2;
   static constexpr int kTabB = (kCols + kRows) * KSF * 4;
   static constexpr int kBasB = 3 * KSF * 4;              // 1, u_x, u_y per point
@@ -939,7 +945,76 @@ struct ShapeLayout {
   static constexpr int kList0 = (kCode0 + kRows * kCols + 15) / 16 * 16;
   static constexpr int kBytes = kList0 + kListB;
   static_assert(kBytes <= kLdsBytes, "LDS budget");
+  static_assert(kRaw0 % 16 == 0 && kRawB % 16 == 0 && kRawRows % 4 == 0, "16-byte rows");
 };
+
+// Producers of pass 2: a raw chunk with its attributes by 16 bytes, global ->
+// registers -> LDS, in the order of raw_load_rows with four attributes in the
+// place of one (a point's rows are only 4-byte aligned, which a global load
+// takes).  A slab's last load may take attributes of the next slab, which
+// nothing reads; past the point's own it takes single ones.  Against 4 bytes a
+// load, which cost the producers more instructions than the terms: 50,000
+// points, 64 attributes, 2048^2 (bfloat16) 9.54 -> 7.79 ms.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int IT>
+__device__ __forceinline__ void quad_load(const LPParams& p, const Chunk& ch, int64_t base,
+                                          const uint16_t* list, int d0, int quads,
+                                          const RowWalk& rw, int pt, f32x4 (&r)[IT],
+                                          float& rxy) {
+  typedef const __attribute__((address_space(1))) char* Bytes;
+  const Bytes pts = (Bytes)(global_ptr(p.pts) + 2 * base);
+  const Bytes vals = (Bytes)(global_ptr(p.vals) + base * p.D + d0);
+  auto at = [](Bytes b, uint32_t off) {
+    return *(const __attribute__((address_space(1))) float*)(b + off);
+  };
+  const uint16_t* lk = list + ch.k;
+  const int kn = ch.kn, width = p.D - d0;
+  rxy = 0.0f;
+  if (pt < 2 * KT && (pt & (KT - 1)) < kn)
+    rxy = at(pts, 8u * lk[pt & (KT - 1)] + (pt >= KT ? 4u : 0u));
+  int k = rw.k0, q = rw.d0;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (k < kn) {
+      const uint32_t off = 4u * ((uint32_t)lk[k] * (uint32_t)p.D + 4u * (uint32_t)q);
+      if (4 * q + 4 <= width) {
+        v = *(const __attribute__((address_space(1))) f32x4u*)(vals + off);
+      } else {
+        v[0] = at(vals, off);
+        if (4 * q + 1 < width) v[1] = at(vals, off + 4);
+        if (4 * q + 2 < width) v[2] = at(vals, off + 8);
+      }
+    }
+    r[it] = v;
+    k += rw.ks;
+    q += rw.ds;
+    if (q >= quads) {
+      q -= quads;
+      ++k;
+    }
+  }
+}
+
+template <int IT>
+__device__ __forceinline__ void quad_store(float* raw, int rows, int stride, int quads,
+                                           const RowWalk& rw, int pt, const f32x4 (&r)[IT],
+                                           float rxy) {
+  if (pt < 2 * KT) raw[(pt / KT) * RS + (pt & (KT - 1))] = rxy;
+  int k = rw.k0, q = rw.d0;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    if (k < KT) *(f32x4*)(raw + rows + k * stride + 4 * q) = r[it];
+    k += rw.ks;
+    q += rw.ds;
+    if (q >= quads) {
+      q -= quads;
+      ++k;
+    }
+  }
+}
 
 // Producer: the separable Gaussian tables of a chunk (32 rows: 16 node
 // columns, then 16 node rows, x 64 points; zero past the chunk).
@@ -1039,11 +1114,16 @@ __device__ __forceinline__ void shape_chunk(const LPParams& p, const float* raw,
       bas[j * KSF + k0] = mo0[j];
       bas[j * KSF + k0 + 1] = mo1[j];
     }
-  const float* rv = raw + 2 * RS;
+  const float* r0 = raw + L::kRawRows + k0 * L::kRawStride;
   const float a0 = mo0[0] * AttrGain<T>::value, a1 = mo1[0] * AttrGain<T>::value;
-  for (int d = g; d < nv; d += 8)
-    emit_terms<kShapeS2, T>(G + (size_t)d * KSH + k0, (size_t)L::kDs * KSH, a0 * rv[d * RS + k0],
-                            a1 * rv[d * RS + k0 + 1]);
+  for (int d = 4 * g; d < nv; d += 32) {   // four attributes at a time
+    const f32x4 v0 = *(const f32x4*)(r0 + d), v1 = *(const f32x4*)(r0 + L::kRawStride + d);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (d + j < nv)
+        emit_terms<kShapeS2, T>(G + (size_t)(d + j) * KSH + k0, (size_t)L::kDs * KSH, a0 * v0[j],
+                                a1 * v1[j]);
+  }
 }
 
 // The power of two that brings an effective weight's bound, `b`, to 2^14 ..
@@ -1117,6 +1197,7 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
   };
   // producers: a chunk's loads, its tables and terms
   const RowWalk rw1 = row_walk(pt, 0);
+  const int quads = (nv + 3) / 4;   // a point's 16-byte loads
   float toff[kTabIt];
   auto make1 = [&](const Chunk& ch, int b) {
     shape_chunk<DEG, NTV, S1, T, false>(p, raw(b), ch.kn, 0, tab(b), bas(b), feat(b), pt, toff,
@@ -1129,14 +1210,15 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
   // the first two raw chunks of a list at `base` to LDS, then chunk 0's tables
   // and terms once the producers' stores are visible (`sync`)
   auto load2 = [&](int64_t base, const Chunk& ch0, const Chunk& ch1) {
-    float ra[L::kRawIt], rb[L::kRawIt], xa = 0.0f, xb = 0.0f;
+    f32x4 ra[L::kRawIt], rb[L::kRawIt];
+    float xa = 0.0f, xb = 0.0f;
     // (the walk's steps made here: held over pass 1 and its solve, they spill)
-    RowWalk rw2 = row_walk(pt, nv);
+    RowWalk rw2 = row_walk(pt, quads);
     asm volatile("" : "+v"(rw2.k0), "+v"(rw2.d0));
-    raw_load_rows(p, ch0, base, list, d0, nv, rw2, pt, ra, xa);
-    raw_load_rows(p, ch1, base, list, d0, nv, rw2, pt, rb, xb);
-    raw_store_rows(raw(0), nv, rw2, pt, ra, xa);
-    raw_store_rows(raw(1), nv, rw2, pt, rb, xb);
+    quad_load(p, ch0, base, list, d0, quads, rw2, pt, ra, xa);
+    quad_load(p, ch1, base, list, d0, quads, rw2, pt, rb, xb);
+    quad_store(raw(0), L::kRawRows, L::kRawStride, quads, rw2, pt, ra, xa);
+    quad_store(raw(1), L::kRawRows, L::kRawStride, quads, rw2, pt, rb, xb);
   };
 
   // ---- pass 1: moments, then the ladder and the shape coefficients ----
@@ -1366,7 +1448,7 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
     }
   } else {
     zero_rows(nv, L::kDs, kShapeS2, pt, kProd);
-    const RowWalk rw2 = row_walk(pt, nv);
+    const RowWalk rw2 = row_walk(pt, quads);
     for (;;) {
       Walker wk{0, kept};
       Chunk ch0 = walker_take(wk);
@@ -1377,12 +1459,13 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
       }
       if (ch0.valid) make2(ch0, 0);
       __syncthreads();
-      float rr[L::kRawIt], rxy = 0.0f;
+      f32x4 rr[L::kRawIt];
+      float rxy = 0.0f;
       for (int c = 0; ch0.valid; ++c) {
         const Chunk ch2 = walker_take(wk);
-        raw_load_rows(p, ch2, base, list, d0, nv, rw2, pt, rr, rxy);
+        quad_load(p, ch2, base, list, d0, quads, rw2, pt, rr, rxy);
         if (ch1.valid) make2(ch1, (c + 1) & 1);
-        raw_store_rows(raw(c & 1), nv, rw2, pt, rr, rxy);
+        quad_store(raw(c & 1), L::kRawRows, L::kRawStride, quads, rw2, pt, rr, rxy);
         __syncthreads();
         ch0 = ch1;
         ch1 = ch2;

@@ -15,8 +15,8 @@
 //     allocates nothing.
 //   - A scheduler thread gives every free slot the next batch: the request
 //     at the head of the queue and the later queued requests of its kernel
-//     class (16-bit one-pass Gaussian fits of one degree, feature-tile
-//     count, term count and format), in arrival order, while their staging
+//     class (16-bit Gaussian fits of one degree, form, tile count, term
+//     count and format), in arrival order, while their staging
 //     fits the slot.  A batch is staged request by request into the slot's
 //     scratch and runs as one persistent kernel whose workgroups take
 //     (request, tile) items from a device counter.  Each request's
@@ -24,7 +24,7 @@
 //     finishes its last item; the scheduler polls the flags and retires
 //     requests one by one while the batch runs on.  A request that arrives
 //     meanwhile joins the next batch a slot takes.  Requests of other kinds
-//     (float64, Wendland, the two-pass bfloat16 form) run alone on a slot,
+//     (float64, Wendland, gradients) run alone on a slot,
 //     their completion signalled by a host function behind them.
 //   - Cancellation (mls_server_cancel, or a request's timeout): a queued
 //     request leaves the queue at once; a batched one has its pinned cancel
