@@ -17,6 +17,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -130,6 +131,11 @@ TRAFFIC_SUMMARIES = {
     "c5_n1000000_d16_quadratic_wendland_h0.01_4096": "fit_lp_c5_traffic.md",
 }
 
+# reach of the Gaussian in units of h: where exp(-r^2 / h^2) falls below the
+# rounding of float64 and of float32 sums, and below float16's range
+GAUSS_REACH = {"f64": math.sqrt(53 * math.log(2)), "bf16": math.sqrt(24 * math.log(2)),
+               "fp16": math.sqrt(27.8)}
+
 # the sources that decide each contraction kernel's memory traffic
 F64_SOURCES = ["paper_1408_0677_amd/csrc/mls_fit_f64_shape.hip",
                "paper_1408_0677_amd/csrc/mls_fit_f64.h", "paper_1408_0677_amd/csrc/mls_solve.h"]
@@ -149,7 +155,7 @@ def serve_bench(args):
     dev = torch.device("cuda:0")
     budget = 2 << 30
     # a slot stages a whole batch (room for about 16 of the largest 16-bit
-    # requests) or one float64 request (its Gaussian factor tables)
+    # requests) or one float64 request
     slot_scratch = max(16 * max(api.fit_scratch_bytes(r.n, r.d, r.grid, "fp16") for r in reqs),
                        max(api.fit_scratch_bytes(r.n, r.d, r.grid, "f64") for r in reqs)) + \
         (1 << 20)
@@ -554,20 +560,25 @@ def fit_step_bench(args, w, prec):
     else:
         pairs = nodes * w.n
         pair_kind = "node-point pairs"
-    flops = 2.0 * F * pairs
+    # the roofline counts the pairs that the fit cannot do without: with the
+    # Gaussian those whose weight its sums can see
+    work_pairs = support_pairs(w.points, w.grid, w.h * GAUSS_REACH[prec]) \
+        if w.weight == "gaussian" else pairs
+    flops = 2.0 * F * work_pairs
     # the two-pass (shape-function) form contracts n_mom + D columns, not
     # n_mom + m D: its roofline counts its own work
-    if form == 2:
-        F_form = moment_terms(w.basis) + w.d
-    else:
-        F_form = F
-    flops_form = 2.0 * F_form * pairs
+    if prec == "f64" and w.weight == "gaussian" and \
+            (w.basis == "quadratic" or (w.basis == "linear" and w.d > 3)):
+        form = 3
+    F_form = moment_terms(w.basis) + w.d if form in (2, 3) else F
+    flops_form = 2.0 * F_form * work_pairs
     ms_per_step = wall * 1e3 / args.steps
     # the contraction kernel's own time, from the library's stage events
     kern_ms = float(np.mean(contract_ms))
     achieved = flops_form / (kern_ms * 1e-3) / 1e12
     if prec == "f64":
-        peak, kernel, sources = PEAK_F64_MFMA_TFLOPS, "fit_f64_kernel", F64_SOURCES
+        peak, sources = PEAK_F64_MFMA_TFLOPS, F64_SOURCES
+        kernel = "fit_f64_shape_kernel" if form == 3 else "fit_f64_kernel"
     else:
         peak, sources = PEAK_BF16_MFMA_TFLOPS, LP_SOURCES
         kernel = "fit_shape_kernel" if form == 2 else "fit_lp_kernel"
@@ -610,7 +621,9 @@ def fit_step_bench(args, w, prec):
                      "traffic": traffic, "kernel": kernel,
                      "algorithmic_flops_per_launch": flops_form,
                      "form": {0: "f64 one pass", 1: "16-bit one pass",
-                              2: "16-bit two passes (shape functions)"}.get(form),
+                              2: "16-bit two passes (shape functions)",
+                              3: "f64 two passes (shape functions)"}.get(form),
+                     "pairs_in_reach": work_pairs,
                      "one_pass_equivalent_tflops": flops / (kern_ms * 1e-3) / 1e12,
                      "kernel_ms": kern_ms},
     }
