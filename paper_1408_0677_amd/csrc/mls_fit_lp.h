@@ -54,9 +54,10 @@
 // instructions per tile, against about 2 us of a compute unit per 64 points
 // contracted.  50,000 points, 64 attributes, h = 0.015, 2048^2 (bfloat16, two
 // passes): 206.3 ms over all points, 14.2 within 8 h (39 chunks a pass), 9.5
-// within the adaptive reach (25), 7.8 with attributes loaded by 16 bytes.
-// There a tile takes 290,000 cycles: 42,000 of listing, 87,000 of pass 1,
-// 13,000 of solves, about 125,000 of pass 2, 18,000 of stores; in pass 2 the
+// within the adaptive reach (25), 7.8 with attributes loaded and 7.55 with
+// fields stored by 16 bytes.
+// There a tile takes 280,000 cycles: 42,000 of listing, 87,000 of pass 1,
+// 13,000 of solves, about 125,000 of pass 2, 10,000 of stores; in pass 2 the
 // vector instructions of the effective weights and the producers bound it, the
 // matrix instructions are a quarter.
 #include <hip/hip_runtime.h>
@@ -1479,6 +1480,9 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
   // scale; lane holds node columns 4 (lane / 16) + r of strip t for attribute
   // q * 16 + lane % 16
   if (mma) {
+    // four columns a store where every row of every plane is 16-byte aligned
+    // (64 attributes, 2048^2: 7.80 -> 7.55 ms)
+    const bool wide = (p.W & 3) == 0 && ((uintptr_t)p.fields & 15) == 0;
 #pragma unroll
     for (int q = 0; q < NTV; ++q) {
       const int dd = q * 16 + (lane & 15);
@@ -1489,15 +1493,22 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
       for (int t = 0; t < R; ++t) {
         const int row = wave * R + t, rg = r0 + row;
         if (rg >= p.H) continue;
+        const int cg = c0 + 4 * (lane >> 4);
+        f32x4 v;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int col = 4 * (lane >> 4) + r, cg = c0 + col;
-          if (cg >= p.W) continue;
-          const int node = row * kCols + col;
+          const int node = row * kCols + 4 * (lane >> 4) + r;
           const bool und = codes[node] == 255;
-          fd[(int64_t)rg * p.W + cg] =
-              und ? __builtin_nanf("")
-                  : (float)(sh + sc * ((double)acc[t][q][r] * (double)back[node]));
+          v[r] = und ? __builtin_nanf("")
+                     : (float)(sh + sc * ((double)acc[t][q][r] * (double)back[node]));
+        }
+        float* out = fd + (int64_t)rg * p.W + cg;
+        if (wide) {
+          if (cg < p.W) *(f32x4*)out = v;   // W is a multiple of four
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (cg + r < p.W) out[r] = v[r];
         }
       }
     }

@@ -292,3 +292,26 @@ def test_bf16_zero_floor_far_from_the_points(torch_dev, n):
                      precision="bf16")
     assert (deg == 0).any() and np.isfinite(F[:, deg == 0]).all()
     assert F[:, deg == 0].min() >= -0.01 and F[:, deg == 0].max() <= 1.01
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("width", [1, 3, 4, 17, 20, 64])
+def test_two_pass_stores(torch_dev, prec, width):
+    """Planes of any width at any float address: four columns a store where
+    every row is 16-byte aligned, one elsewhere, the same values, nothing
+    around them."""
+    from paper_1408_0677_amd import api, workloads as wl
+    note(f"case two pass stores {prec} width={width}")
+    rng = np.random.default_rng(width)
+    P = torch_dev.from_numpy(wl.uniform_points(rng, 500).astype(np.float32)).cuda()
+    V = torch_dev.from_numpy(rng.random((500, 19)).astype(np.float32)).cuda()
+    grid = {"x0": 0.1, "y0": 0.1, "dx": 0.006, "dy": 0.006, "width": width, "height": 21}
+    count = 19 * 21 * width
+    got = []
+    for off in (0, 1, 4):
+        buf = torch_dev.full((count + 16,), 7.0, device="cuda")
+        api.fit(P, V, grid, basis="linear", h=0.12, precision=prec, lp_form=2,
+                out=buf[off:off + count].view(19, 21, width))
+        assert bool((buf[:off] == 7.0).all()) and bool((buf[off + count:] == 7.0).all())
+        got.append(buf[off:off + count].view(torch_dev.int32).clone())
+    assert torch_dev.equal(got[0], got[1]) and torch_dev.equal(got[0], got[2])
