@@ -14,10 +14,12 @@
 // takes it attribute-major, vals_t[d][i], and sorts each row into cell order
 // (mls_cells.hip).  Bound: HBM (one read of values, one write).
 //
-// An attribute with a NaN takes a NaN shift and scale: the NaN reaches every
-// node of its field, as it does when all points are summed (0 x NaN), also
-// where the tile never meets the point.  An infinite value does so by itself
-// (an infinite range).
+// Point-major, an attribute with a NaN takes a NaN shift and scale: the NaN
+// reaches every node of its field, as it does when all points are summed (0 x
+// NaN), also where the tile never meets the point.  Attribute-major the range
+// is that of the other values and the NaN stays at its point, so that only the
+// tiles that list the point see it, as the compact support means it.  An
+// infinite value reaches every node either way (an infinite range).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -37,12 +39,15 @@ constexpr int64_t kFusedRanges = 2048;
 constexpr int kMaxAttrs = 1024;     // attributes of a 16-bit fit
 static_assert(MLS_MAX_D_LP <= kMaxAttrs, "attributes in LDS");
 
-// min and max that return NaN when either operand is one.
-__device__ __forceinline__ float nan_min(float a, float b) {
-  return a != a || b != b ? a + b : fminf(a, b);
+// min and max that return NaN when either operand is one (KEEP) or the other
+// operand then.
+template <bool KEEP>
+__device__ __forceinline__ float range_min(float a, float b) {
+  return KEEP && (a != a || b != b) ? a + b : fminf(a, b);
 }
-__device__ __forceinline__ float nan_max(float a, float b) {
-  return a != a || b != b ? a + b : fmaxf(a, b);
+template <bool KEEP>
+__device__ __forceinline__ float range_max(float a, float b) {
+  return KEEP && (a != a || b != b) ? a + b : fmaxf(a, b);
 }
 
 // Partial min / max of each attribute over a block of rows.  Block (32, 32):
@@ -50,6 +55,7 @@ __device__ __forceinline__ float nan_max(float a, float b) {
 // threadIdx.y the block's rows, 32 at a time and four such steps in flight
 // (a block is a chain of loads: 8 rows at a time, one in flight, took 19 us
 // for 20,011 points of 5 attributes where this takes 8.6).
+template <bool KEEP>
 __global__ __launch_bounds__(32 * kRangeRows) void attr_range_kernel(const float* vals, int64_t n,
                                                                      int D, float* pmin,
                                                                      float* pmax) {
@@ -57,7 +63,6 @@ __global__ __launch_bounds__(32 * kRangeRows) void attr_range_kernel(const float
   const int d = blockIdx.y * 32 + threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlock;
   const int64_t r1 = r0 + kRowsPerBlock < n ? r0 + kRowsPerBlock : n;
-  // min and max that keep a NaN once they have met one
   float lo = INFINITY, hi = -INFINITY;
   if (d < D) {
     for (int64_t r = r0 + threadIdx.y; r < r1; r += 4 * kRangeRows) {
@@ -69,8 +74,8 @@ __global__ __launch_bounds__(32 * kRangeRows) void attr_range_kernel(const float
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        lo = nan_min(lo, v[q]);
-        hi = nan_max(hi, v[q]);
+        lo = range_min<KEEP>(lo, v[q]);
+        hi = range_max<KEEP>(hi, v[q]);
       }
     }
   }
@@ -80,9 +85,9 @@ __global__ __launch_bounds__(32 * kRangeRows) void attr_range_kernel(const float
   for (int half = kRangeRows / 2; half > 0; half /= 2) {
     if ((int)threadIdx.y < half) {
       smin[threadIdx.y][threadIdx.x] =
-          nan_min(smin[threadIdx.y][threadIdx.x], smin[threadIdx.y + half][threadIdx.x]);
+          range_min<KEEP>(smin[threadIdx.y][threadIdx.x], smin[threadIdx.y + half][threadIdx.x]);
       smax[threadIdx.y][threadIdx.x] =
-          nan_max(smax[threadIdx.y][threadIdx.x], smax[threadIdx.y + half][threadIdx.x]);
+          range_max<KEEP>(smax[threadIdx.y][threadIdx.x], smax[threadIdx.y + half][threadIdx.x]);
     }
     __syncthreads();
   }
@@ -103,6 +108,7 @@ __device__ __forceinline__ void range_map(float lo, float hi, float* shift, floa
 
 // Shift and scale of attributes d0 .. d0 + nd of the partial ranges into LDS,
 // by the block's threads (`t` of `threads`); the caller synchronises.
+template <bool KEEP>
 __device__ __forceinline__ void fused_map(const float* pmin, const float* pmax, int nblk, int D,
                                           int d0, int nd, int t, int threads, float* sshift,
                                           float* sscale) {
@@ -110,8 +116,8 @@ __device__ __forceinline__ void fused_map(const float* pmin, const float* pmax, 
     float lo = INFINITY, hi = -INFINITY;
 #pragma unroll 8
     for (int b = 0; b < nblk; ++b) {
-      lo = nan_min(lo, pmin[(int64_t)b * D + d0 + d]);
-      hi = nan_max(hi, pmax[(int64_t)b * D + d0 + d]);
+      lo = range_min<KEEP>(lo, pmin[(int64_t)b * D + d0 + d]);
+      hi = range_max<KEEP>(hi, pmax[(int64_t)b * D + d0 + d]);
     }
     range_map(lo, hi, sshift + d, sscale + d);
   }
@@ -119,6 +125,7 @@ __device__ __forceinline__ void fused_map(const float* pmin, const float* pmax, 
 
 // One block per attribute: min / max over the partial ranges (min and max
 // are exact, so the order of the reduction does not matter).
+template <bool KEEP>
 __global__ __launch_bounds__(256) void attr_finalize_kernel(const float* pmin, const float* pmax,
                                                             int nblk, int D, float* shift,
                                                             float* scale) {
@@ -127,13 +134,13 @@ __global__ __launch_bounds__(256) void attr_finalize_kernel(const float* pmin, c
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   float lo = INFINITY, hi = -INFINITY;
   for (int b = t; b < nblk; b += 256) {
-    lo = nan_min(lo, pmin[(int64_t)b * D + d]);
-    hi = nan_max(hi, pmax[(int64_t)b * D + d]);
+    lo = range_min<KEEP>(lo, pmin[(int64_t)b * D + d]);
+    hi = range_max<KEEP>(hi, pmax[(int64_t)b * D + d]);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    lo = nan_min(lo, __shfl_xor(lo, o, 64));
-    hi = nan_max(hi, __shfl_xor(hi, o, 64));
+    lo = range_min<KEEP>(lo, __shfl_xor(lo, o, 64));
+    hi = range_max<KEEP>(hi, __shfl_xor(hi, o, 64));
   }
   if (lane == 0) {
     slo[wave] = lo;
@@ -141,8 +148,8 @@ __global__ __launch_bounds__(256) void attr_finalize_kernel(const float* pmin, c
   }
   __syncthreads();
   if (t != 0) return;
-  lo = nan_min(nan_min(slo[0], slo[1]), nan_min(slo[2], slo[3]));
-  hi = nan_max(nan_max(shi[0], shi[1]), nan_max(shi[2], shi[3]));
+  lo = range_min<KEEP>(range_min<KEEP>(slo[0], slo[1]), range_min<KEEP>(slo[2], slo[3]));
+  hi = range_max<KEEP>(range_max<KEEP>(shi[0], shi[1]), range_max<KEEP>(shi[2], shi[3]));
   range_map(lo, hi, shift + d, scale + d);
 }
 
@@ -160,7 +167,7 @@ __global__ __launch_bounds__(256) void stage_values_kernel(const float* vals, in
   const int nd = D - d0 < 32 ? D - d0 : 32;
   const int t = threadIdx.y * 32 + threadIdx.x;
   if (nblk > 0) {
-    fused_map(pmin, pmax, nblk, D, d0, nd, t, 256, sshift, sscale);
+    fused_map<false>(pmin, pmax, nblk, D, d0, nd, t, 256, sshift, sscale);
     if (blockIdx.x == 0 && t < nd) {
       shift[d0 + t] = sshift[t];
       scale[d0 + t] = sscale[t];
@@ -195,7 +202,7 @@ __global__ __launch_bounds__(256) void stage_rows_kernel(const float* vals, int6
   __shared__ float sshift[kMaxAttrs], sscale[kMaxAttrs];
   const int t = threadIdx.x;
   if (nblk > 0) {
-    fused_map(pmin, pmax, nblk, D, 0, D, t, 256, sshift, sscale);
+    fused_map<true>(pmin, pmax, nblk, D, 0, D, t, 256, sshift, sscale);
     // a thread stores what it found itself
     for (int d = t; blockIdx.x == 0 && d < D; d += 256) {
       shift[d] = sshift[d];
@@ -218,17 +225,18 @@ __global__ __launch_bounds__(256) void stage_rows_kernel(const float* vals, int6
 
 int64_t stage_partial_blocks(int64_t n) { return (n + kRowsPerBlock - 1) / kRowsPerBlock; }
 
-hipError_t launch_stage(const float* vals, int64_t n, int D, float* pmin, float* pmax,
-                        float* shift, float* scale, float* vals_s, bool rows, hipStream_t s) {
+template <bool ROWS>
+static hipError_t launch_stage_impl(const float* vals, int64_t n, int D, float* pmin, float* pmax,
+                                    float* shift, float* scale, float* vals_s, hipStream_t s) {
   const int64_t nblk = stage_partial_blocks(n);
   const int dblk = (D + 31) / 32;
-  hipLaunchKernelGGL(attr_range_kernel, dim3((unsigned)nblk, dblk), dim3(32, kRangeRows), 0, s,
-                     vals, n, D, pmin, pmax);
+  hipLaunchKernelGGL(attr_range_kernel<ROWS>, dim3((unsigned)nblk, dblk), dim3(32, kRangeRows), 0,
+                     s, vals, n, D, pmin, pmax);
   const int fused = nblk * D <= kFusedRanges ? (int)nblk : 0;
   if (!fused)
-    hipLaunchKernelGGL(attr_finalize_kernel, dim3(D), dim3(256), 0, s, pmin, pmax, (int)nblk, D,
-                       shift, scale);
-  if (rows) {
+    hipLaunchKernelGGL(attr_finalize_kernel<ROWS>, dim3(D), dim3(256), 0, s, pmin, pmax,
+                       (int)nblk, D, shift, scale);
+  if (ROWS) {
     // 1,024 values a block, so that the fused reduction repeats less
     const int64_t nb = (n * D + 1023) / 1024;
     hipLaunchKernelGGL(stage_rows_kernel, dim3((unsigned)(nb < 65536 ? nb : 65536)), dim3(256), 0,
@@ -238,6 +246,12 @@ hipError_t launch_stage(const float* vals, int64_t n, int D, float* pmin, float*
                        0, s, vals, n, D, shift, scale, pmin, pmax, fused, vals_s);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_stage(const float* vals, int64_t n, int D, float* pmin, float* pmax,
+                        float* shift, float* scale, float* vals_s, bool rows, hipStream_t s) {
+  return rows ? launch_stage_impl<true>(vals, n, D, pmin, pmax, shift, scale, vals_s, s)
+              : launch_stage_impl<false>(vals, n, D, pmin, pmax, shift, scale, vals_s, s);
 }
 
 }  // namespace mls
