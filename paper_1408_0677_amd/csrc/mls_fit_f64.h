@@ -51,6 +51,7 @@ struct F64Params {
 };
 
 constexpr double kFineSpan = 8.0;
+constexpr double kFineReach2 = 18.0 * 18.0;
 
 // Weight modes of the kernel: the Gaussian, the inverse-distance weight per
 // pair (any exponent, or alpha = 1 and alpha = 2 through a reciprocal).
@@ -187,11 +188,13 @@ __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, dou
 // lower).  They follow by stepping: g_{c+1} / g_c = exp(2 s (u - e_c) - s^2),
 // and that ratio itself shrinks by q = exp(-2 s^2) per step: two
 // multiplications per node after two exponentials.
-// On fine grids (kFineSpan), for a list within reach, one thread steps through a half from its first
-// node: the exponents stay above -(8.5 + 8)^2, far from
-// underflow.  Otherwise start at the node nearest to u (the largest factor),
-// so that every exponent is <= 0; the upper half's thread steps up from it
-// and the lower half's down.
+// On fine grids (kFineSpan), for a list within a reach of kFineReach2, one
+// thread steps through a half from its first node: a listed point is at most
+// R + 8 h from it, and the exponents stay above -(18 + 8)^2 = -676, short of
+// where exp loses digits (-708).  Otherwise (a tiny weight floor makes R as
+// large as 27) start at the node nearest to u (the largest factor), so that
+// every exponent is <= 0; the upper half's thread steps up from it and the
+// lower half's down.
 template <int CNT>
 __device__ __forceinline__ void gauss_steps(bool fine, double u, double s, double q, bool up,
                                             double* g) {

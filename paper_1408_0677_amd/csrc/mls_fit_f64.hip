@@ -249,7 +249,7 @@ void fit_f64_kernel(F64Params p) {
     const int kn = (int)((cnt - k0) < KT ? (cnt - k0) : KT);
     if constexpr (!INV) {
       // 2a. separable Gaussian factors
-      put_gauss<L::kRows>(p.fine && reach.r2 < __builtin_inf(), ux, uy, gx, kn, sx, sy, qx, qy, tid);
+      put_gauss<L::kRows>(p.fine && reach.r2 <= kFineReach2, ux, uy, gx, kn, sx, sy, qx, qy, tid);
     } else {
       // inverse-distance weights do not separate: the tables hold the squared
       // node offsets, and the A operand forms the weight per pair

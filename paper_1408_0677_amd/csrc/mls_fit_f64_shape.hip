@@ -132,7 +132,7 @@ void fit_f64_shape_kernel(F64Params p) {
       acc4[t][0] = acc4[t][1] = 0.0;
     }
     for (int e = tid; e < (L::kFP1 - L::nmom) * KS; e += kThreads) G[L::nmom * KS + e] = 0.0;
-    fine = p.fine && reach.r2 < __builtin_inf();
+    fine = p.fine && reach.r2 <= kFineReach2;
     segments = 0;
     for (int64_t pos = 0; pos < p.n; ++segments) {
       next_list(pos);

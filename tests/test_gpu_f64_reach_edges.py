@@ -1,0 +1,65 @@
+"""Float64 Gaussian fits where what lies beyond the usual reach decides:
+weight floors small enough that far points determine a node, and attributes
+whose sizes differ by more than the weights."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def gpu_fit(torch, pts, vals, grid, **kw):
+    from paper_1408_0677_amd import api
+    P = torch.from_numpy(np.ascontiguousarray(pts, np.float32)).cuda()
+    V = torch.from_numpy(np.ascontiguousarray(vals, np.float32)).cuda()
+    f, d = api.fit(P, V, grid, **kw)
+    torch.cuda.synchronize()
+    return f.cpu().numpy().reshape(V.shape[1], -1), d.cpu().numpy().ravel()
+
+
+# the cluster right of the grid and left of it, above and below (each half of a
+# tile starts its factors at one end), tiles of 4 rows and of 16
+@pytest.mark.parametrize("side", ["right", "left", "above", "below"])
+@pytest.mark.parametrize("width,height", [(23, 23), (23, 4200)])
+@pytest.mark.parametrize("basis,d", [("constant", 3), ("linear", 5)])
+def test_tiny_weight_floor(torch_dev, oracle, basis, d, width, height, side):
+    """Nodes 17 h to 29 h from a cluster of points, on tiles of 8 h, with a
+    weight floor of 1e-300: determined up to 26.3 h.  The factors of a half tile
+    whose first node is 28 h away underflow there and not at its last node."""
+    print(f"case tiny floor {basis} {side} {width} x {height}", flush=True)
+    rng = np.random.default_rng(3)
+    h = 0.01
+    dx = 8.0 / 15.0 * h
+    if side in ("above", "below"):
+        width, height = height, width
+    pts = (0.02 * h * rng.random((500, 2))).astype(np.float32)
+    vals = rng.random((500, d)).astype(np.float32)
+    grid = {"x0": -3 * dx, "y0": -3 * dx, "dx": dx, "dy": dx, "width": width, "height": height}
+    if side == "right":
+        grid["x0"] = -29.0 * h
+    elif side == "left":
+        grid["x0"] = 17.0 * h
+    elif side == "above":
+        grid["y0"] = -29.0 * h
+    else:
+        grid["y0"] = 17.0 * h
+    kw = dict(basis=basis, h=h, weight_floor=1e-300)
+    F, deg = gpu_fit(torch_dev, pts, vals, grid, **kw)
+    of, od, dm = oracle.fit_grid(pts, vals, grid, **kw)
+    of, od = of.reshape(d, -1), od.ravel()
+    assert (od != 255).any() and (od == 255).any()
+    # (the ladder's degrees above 0 are rounding noise: the cluster is a point
+    # from there)
+    assert np.array_equal(deg == 255, od == 255)
+    both = (deg == 0) & (od == 0)
+    if basis == "constant":
+        assert both.sum() == (od == 0).sum()
+    if both.any():
+        assert np.abs(F - of)[:, both].max() <= 1e-5
