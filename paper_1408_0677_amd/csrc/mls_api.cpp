@@ -45,9 +45,9 @@ struct mls_context {
   Scratch scratch;
   // fit staging: attribute ranges, shift/scale, normalised values
   Scratch fit_scratch;
-  // words of the float64 fit's look for inputs that are not finite, for the
+  // words of the float64 fit's look over its inputs (mls_internal.h), for the
   // context's lifetime
-  uint32_t* bad = nullptr;
+  uint32_t* words = nullptr;
 
   // pinned host word for counts read back by mls_contour
   int64_t* pinned = nullptr;
@@ -121,6 +121,26 @@ mls_status ensure_scratch(Scratch& sc, size_t bytes) {
     return fail(MLS_ERR_OUT_OF_MEMORY, "scratch allocation of %zu bytes failed", want);
   }
   sc.bytes = want;
+  return MLS_OK;
+}
+
+// Make sure the context has its words, zero at first.
+mls_status ensure_words(mls_context* ctx) {
+  if (ctx->words) return MLS_OK;
+  const size_t bytes = sizeof(uint32_t) * mls::kF64Words;
+  void* w = nullptr;
+  hipError_t e = hipMalloc(&w, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(MLS_ERR_OUT_OF_MEMORY, "scratch allocation of %zu bytes failed", bytes);
+  }
+  e = hipMemset(w, 0, bytes);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) {
+    (void)hipFree(w);
+    return device_fail(e, "hipMemset (context words)");
+  }
+  ctx->words = (uint32_t*)w;
   return MLS_OK;
 }
 
@@ -397,16 +417,16 @@ mls_status mls_context_create(int32_t device, mls_context** out) {
     delete ctx;
     return device_fail(e, "hipEventCreateWithFlags");
   }
-  e = hipMalloc((void**)&ctx->bad, sizeof(uint32_t) * mls::kF64BadWords);
-  if (e != hipSuccess) {
+  const mls_status st = ensure_words(ctx);
+  if (st != MLS_OK) {
     (void)hipEventDestroy(ctx->last_use);
     delete ctx;
-    return device_fail(e, "hipMalloc (context words)");
+    return st;
   }
   // the fixed scratch of mls_contour_static: its address on this device
   e = mls::contour_static_scratch_resolve(device);
   if (e != hipSuccess) {
-    (void)hipFree(ctx->bad);
+    (void)hipFree(ctx->words);
     (void)hipEventDestroy(ctx->last_use);
     delete ctx;
     return device_fail(e, "hipGetSymbolAddress (contour scratch)");
@@ -421,7 +441,7 @@ void mls_context_destroy(mls_context* ctx) {
     for (TraceCall& c : ctx->trace.pending) trace_destroy(c);
     if (ctx->scratch.ptr) (void)hipFree(ctx->scratch.ptr);
     if (ctx->fit_scratch.ptr) (void)hipFree(ctx->fit_scratch.ptr);
-    if (ctx->bad) (void)hipFree(ctx->bad);
+    if (ctx->words) (void)hipFree(ctx->words);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->last_use) (void)hipEventDestroy(ctx->last_use);
   }
@@ -571,7 +591,7 @@ mls_status fit_prepare(mls_context* ctx, const float* d_points, const float* d_v
   a.deg_out = d_degree;
   a.grads = d_grad;
   a.lp_form = form;
-  a.bad = nullptr;
+  a.words = nullptr;
   *out = a;
   *terms_out = terms;
   return MLS_OK;
@@ -621,7 +641,7 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
         (st = ensure_scratch(ctx->fit_scratch, plan.total)) != MLS_OK)
       return st;
     if ((st = scratch_acquire(ctx, s)) != MLS_OK) return st;
-    a.bad = ctx->bad;
+    a.words = ctx->words;
     e = mls::launch_fit_f64(a, s);
     if (e != hipSuccess) return device_fail(e, "fit kernel launch");
     tr.set_form(0);
@@ -651,8 +671,6 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
       e = mls::launch_hits(hta, s);
       if (e != hipSuccess) return device_fail(e, "exact-hit pass launch");
       tr.mark("hits");
-      tr.finish();
-      return scratch_release(ctx, s);
     }
     tr.finish();
     return scratch_release(ctx, s);

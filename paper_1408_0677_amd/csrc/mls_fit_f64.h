@@ -41,11 +41,10 @@ struct F64Params {
   uint8_t* deg_out;
   float* grads;        // [D][2][H][W] or null
   bool rigid;          // rigid map (EPI 2 kernels)
-  // Gaussian: reach of the tiles (tile_reach), whether an input that is not
-  // finite was found (words of finite_kernel; none: the tiles look themselves)
+  // Gaussian: reach of the tiles (tile_reach), and the result of the look over
+  // the attributes' sizes (look_kernel; null: the tiles look themselves)
   double list_log;     // ln n + 54 ln 2, or infinite: every tile sums all points
-  const uint32_t* bad;
-  int n_bad;
+  const uint32_t* sizes;
   bool vec4;           // rows of the fields are 16-byte aligned
   bool fine;           // a tile spans at most kFineSpan h on either axis
 };
@@ -97,7 +96,42 @@ __device__ __forceinline__ void read4(const double* src, double* dst) {
 // moment is itself below 2^-14 of that scale (its near points all on one
 // line through it, say) could still see what is left out above 2^-40: its
 // tile is then summed again over all points (kDiagFloor).
+//
+// The products with an attribute see the weights times its values, and a value
+// far away may be larger than those near a node by more than the weights fall
+// (a marker of 1e30 for a missing value, an attribute that grows
+// exponentially).  So what is left out has to be small against the attribute's
+// smallest magnitude other than 0: where the largest is more than 2^kSizeFree
+// times that, the bound above is taken smaller by the rest, which leaves at
+// most 2^-30 of what the near points add, a 64th of the float32 result's
+// rounding.  Attributes of up to 2^24 from the smallest to the largest, which
+// is most, have the reach of the weights alone.
 constexpr double kDiagFloor = 0x1p-14;
+constexpr int kSizeFree = 24;
+constexpr int kSizeNotFinite = 1 << 20;
+
+// Magnitudes of an attribute as bits of |f|, which order as the values do:
+// the largest, and the smallest other than 0.
+struct Sizes {
+  uint32_t hi = 0, lo = 0x7F800000u;
+  __device__ __forceinline__ void add(float f) {
+    const uint32_t m = __builtin_bit_cast(uint32_t, f) & 0x7FFFFFFFu;
+    hi = m > hi ? m : hi;
+    lo = m != 0 && m < lo ? m : lo;
+  }
+};
+
+// Binary digits that the bound gains for an attribute: at least the log2 of
+// the ratio of its sizes, less kSizeFree; kSizeNotFinite for an infinity or a
+// NaN.
+__device__ __forceinline__ int size_digits(uint32_t hi, uint32_t lo) {
+  if (hi >= 0x7F800000u) return kSizeNotFinite;
+  if (hi == 0) return 0;
+  // (subnormal numbers go down to 2^-149, the exponent field of 2^-126 being 1)
+  const int eh = (int)(hi >> 23), el = lo >> 23 ? (int)(lo >> 23) : -22;
+  const int digits = (eh > 1 ? eh : 1) + 1 - el - kSizeFree;
+  return digits > 0 ? digits : 0;
+}
 
 // A value that is the same in every lane, into scalar registers.
 __device__ __forceinline__ double uniform(double v) {
@@ -124,11 +158,36 @@ __device__ __forceinline__ bool in_reach(const F64Reach& t, float x, float y) {
   return !(ax * ax + ay * ay > t.r2);
 }
 
+// The look over n x D values by the workgroup's threads (the first
+// threads / D * D of them: each keeps to one attribute), into LDS words hi[D]
+// and lo[D], which the caller has set to 0 and 0x7F800000 before a barrier and
+// reads after one.  A coordinate that is not finite counts as an attribute 0
+// that is not.  Elements are taken from block `b` of `nb`.
+__device__ __forceinline__ void look_sizes(const float* vals, int64_t n, int D, const float* pts,
+                                           int b, int nb, uint32_t* hi, uint32_t* lo) {
+  const auto v = global_ptr(vals);
+  const auto q = global_ptr(pts);
+  const int tid = threadIdx.x, per = kThreads / D * D;
+  Sizes sz;
+  if (tid < per) {
+    const int64_t step = (int64_t)nb * per, total = n * D;
+#pragma unroll 4
+    for (int64_t e = (int64_t)b * per + tid; e < total; e += step) sz.add(v[e]);
+    atomicMax(hi + tid % D, sz.hi);
+    atomicMin(lo + tid % D, sz.lo);
+  }
+  bool bad = false;
+#pragma unroll 4
+  for (int64_t e = (int64_t)b * kThreads + tid; e < 2 * n; e += (int64_t)nb * kThreads)
+    bad |= !(fabsf(q[e]) < __builtin_inff());
+  if (bad) atomicMax(hi, 0x7F800000u);
+}
+
 // The reach of the tile whose anchor node is (c0 + 8, r0 + rows / 2).  Every
-// thread of the workgroup calls it; `shared` is LDS for kWaves floats, and
-// the call ends with a barrier.  S is the sum over the points of the weight
-// at their farthest node of the tile; below 1,024 points, where a pass over
-// them costs as much as it saves, S = 0.
+// thread of the workgroup calls it; `shared` is LDS for kWaves floats and 2 D
+// words, and the call ends with a barrier.  S is the sum over the points of
+// the weight at their farthest node of the tile; below 1,024 points, where a
+// pass over them costs as much as it saves, S = 0.
 template <int DEG>
 __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, double cx, double cy,
                                                float* shared) {
@@ -140,10 +199,23 @@ __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, dou
   // a little more than half the rectangle: the test's own rounding
   t.ex = uniform(0.5 * (double)(kCols - 1) * fabs(p.dx) * p.inv_h + 0x1p-40 * (1.0 + fabs(t.ox)));
   t.ey = uniform(0.5 * (double)(rows - 1) * fabs(p.dy) * p.inv_h + 0x1p-40 * (1.0 + fabs(t.oy)));
+  t.scale = uniform(p.floor_w);
+  t.r2 = __builtin_inf();
+  if (!(p.list_log < __builtin_inf())) return t;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int D = p.D;
+  uint32_t* hi = (uint32_t*)shared + kWaves;
+  uint32_t* lo = hi + D;
+  if (!p.sizes) {
+    if (tid < D) {
+      hi[tid] = 0;
+      lo[tid] = 0x7F800000u;
+    }
+    __syncthreads();
+  }
   const auto pts = global_ptr(p.pts);
   float S = 0.0f;
-  if (p.n >= 1024 && p.list_log < __builtin_inf()) {
+  if (p.n >= 1024) {
 #pragma unroll 4
     for (int i = tid; i < (int)p.n; i += kThreads) {
       const float ax = (float)(fabs(fma((double)pts[2 * i], p.inv_h, -t.ox)) + t.ex);
@@ -153,28 +225,27 @@ __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, dou
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
   }
-  // inputs that are not finite reach every node (0 x NaN): sum all points
-  bool bad = !(S < __builtin_inff());
-  if (p.n_bad > 0) {
-    for (int i = tid; i < p.n_bad; i += kThreads) bad = bad || p.bad[i] != 0;
-  } else {
-    const auto vals = global_ptr(p.vals);
-    const int nv = (int)p.n * p.D;
-#pragma unroll 4
-    for (int i = tid; i < nv; i += kThreads) bad |= !(fabsf(vals[i]) < __builtin_inff());
-    for (int i = tid; i < 2 * (int)p.n; i += kThreads)
-      bad |= !(fabsf(pts[i]) < __builtin_inff());
-  }
+  if (!p.sizes) look_sizes(p.vals, p.n, D, p.pts, 0, 1, hi, lo);
   if (lane == 0) shared[wave] = S;
-  const int any = __syncthreads_or(bad);
+  __syncthreads();
   S = 0.0f;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) S += shared[w];
+  int digits = 0;
+  if (p.sizes) {
+    digits = (int)*global_ptr(p.sizes);
+  } else {
+    for (int d = lane; d < D; d += 64) digits = max(digits, size_digits(hi[d], lo[d]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) digits = max(digits, __shfl_xor(digits, o, 64));
+  }
+  digits = __builtin_amdgcn_readfirstlane(digits);
   __syncthreads();
+  // inputs that are not finite reach every node (0 x NaN): sum all points
+  const bool any = digits >= kSizeNotFinite || !(S < __builtin_inff());
   t.scale = uniform(fmax(0.99 * (double)S, p.floor_w));
-  t.r2 = __builtin_inf();
-  if (!any && t.scale > 0.0 && p.list_log < __builtin_inf()) {
-    const double L = p.list_log - log(t.scale);
+  if (!any && t.scale > 0.0) {
+    const double L = p.list_log + (double)digits * 0.6931471805599453 - log(t.scale);
     double r2 = L;
 #pragma unroll
     for (int it = 0; it < 4; ++it) r2 = L + DEG * log(r2);

@@ -509,19 +509,51 @@ hipError_t launch_kind(const F64Params& p, int degree, int nt, hipStream_t s) {
   }
 }
 
-// bad[block] = whether the block met a value or coordinate that is not finite.
-__global__ __launch_bounds__(256) void finite_kernel(const float* __restrict__ vals,
-                                                     int64_t total,
-                                                     const float* __restrict__ pts, int64_t n2,
-                                                     uint32_t* bad) {
-  bool b = false;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n2; i += (int64_t)gridDim.x * 256)
-    b = b || !(fabsf(pts[i]) < __builtin_inff());
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
-       i += (int64_t)gridDim.x * 256)
-    b = b || !(fabsf(vals[i]) < __builtin_inff());
-  const int any = __syncthreads_or(b);
-  if (threadIdx.x == 0) bad[blockIdx.x] = any ? 1u : 0u;
+// The look over the inputs for all tiles: words[1] = the digits (size_digits)
+// that the bound gains, the most of any attribute.  Every block leaves its part
+// in words[2 ..]; the one that finishes last takes them together and sets the
+// count, words[0], back to zero.
+__global__ __launch_bounds__(kThreads) void look_kernel(const float* vals, int64_t n, int D,
+                                                        const float* pts, uint32_t* words) {
+  __shared__ uint32_t hi[kF64MaxAttrs], lo[kF64MaxAttrs];
+  __shared__ uint32_t last;
+  const int tid = threadIdx.x, nb = gridDim.x;
+  if (tid < D) {
+    hi[tid] = 0;
+    lo[tid] = 0x7F800000u;
+  }
+  __syncthreads();
+  look_sizes(vals, n, D, pts, blockIdx.x, nb, hi, lo);
+  __syncthreads();
+  uint32_t* part = words + 2;
+  if (tid < D) {
+    part[(blockIdx.x * D + tid) * 2] = hi[tid];
+    part[(blockIdx.x * D + tid) * 2 + 1] = lo[tid];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  if (tid == 0) last = atomicAdd(words, 1u) == (uint32_t)nb - 1u;
+  __syncthreads();
+  if (!last) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  int digits = 0;
+  if (tid < D) {
+    uint32_t h = 0, l = 0x7F800000u;
+#pragma unroll 8
+    for (int b = 0; b < nb; ++b) {
+      h = max(h, part[(b * D + tid) * 2]);
+      l = min(l, part[(b * D + tid) * 2 + 1]);
+    }
+    digits = size_digits(h, l);
+  }
+  if (tid == 0) hi[0] = 0;
+  __syncthreads();
+  atomicMax(hi, (uint32_t)digits);
+  __syncthreads();
+  if (tid == 0) {
+    words[0] = 0;
+    words[1] = hi[0];
+  }
 }
 
 // Most points for which a tile leaves out those beyond its reach.  The tiles'
@@ -531,9 +563,9 @@ __global__ __launch_bounds__(256) void finite_kernel(const float* __restrict__ v
 // holds a slot with while it sets up, cancels and times out others behind it.
 constexpr int64_t kReachPoints = 32768;
 
-// Values that every tile looks through itself rather than by finite_kernel
+// Values that every tile looks through itself rather than by look_kernel
 // (a launch, about 3 us, against 64 loads per thread).
-constexpr int64_t kFiniteInTile = 16384;
+constexpr int64_t kLookInTile = 16384;
 
 }  // namespace
 
@@ -566,15 +598,13 @@ hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream) {
   }
   hipError_t e;
   p.list_log = a.n <= kReachPoints ? log((double)a.n) + 54.0 * 0.6931471805599453 : HUGE_VAL;
-  p.bad = nullptr;
-  p.n_bad = 0;
+  p.sizes = nullptr;
   p.vec4 = (a.W & 3) == 0 && ((uintptr_t)a.fields & 15) == 0;
-  if (a.n * a.D > kFiniteInTile) {
+  if (f64_needs_words(a.n, a.D)) {
     const int64_t nb = (a.n * a.D + 1023) / 1024;
-    p.bad = a.bad;
-    p.n_bad = (int)(nb < kF64BadWords ? nb : kF64BadWords);
-    hipLaunchKernelGGL(finite_kernel, dim3((unsigned)p.n_bad), dim3(256), 0, stream, a.vals,
-                       a.n * a.D, a.pts, 2 * a.n, a.bad);
+    p.sizes = a.words + 1;
+    hipLaunchKernelGGL(look_kernel, dim3((unsigned)(nb < kF64LookBlocks ? nb : kF64LookBlocks)),
+                       dim3(kThreads), 0, stream, a.vals, a.n, a.D, a.pts, a.words);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const bool shape = !a.rigid && f64_use_shape_form(a.degree, a.D);
@@ -582,6 +612,10 @@ hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream) {
   p.fine = span <= kFineSpan && p.list_log < HUGE_VAL;
   return shape ? launch_fit_f64_shape(p, a.degree, stream)
                : launch_kind<WM_GAUSS>(p, a.degree, nt, stream);
+}
+
+bool f64_needs_words(int64_t n, int32_t D) {
+  return n <= kReachPoints && n * D > kLookInTile;
 }
 
 size_t f64_scratch_bytes(int64_t n, int32_t W, int32_t H) {

@@ -27,7 +27,7 @@ struct FitArgs {
   int32_t lp_form;      // 16-bit paths: 0 the library's choice, 1 one pass, 2 two passes
   float* grads;         // [D][2][H][W] slopes of the local fits, or null
   bool rigid;           // rigid map of 2-vector values (degree 1 moments, D = 2)
-  uint32_t* bad;        // float64 Gaussian: kF64BadWords words of the context
+  uint32_t* words;      // float64 Gaussian, f64_needs_words: kF64Words of the context
 };
 
 // Number of basis terms m and of distinct moment monomials for a degree.
@@ -37,7 +37,14 @@ __host__ __device__ constexpr int moment_terms(int deg) { return deg == 0 ? 1 : 
 // Float64 matrix-core fit (Gaussian or inverse-distance weight).  Returns a
 // hipError_t.  With the inverse-distance weight, launch_hits must follow.
 hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream);
-constexpr int kF64BadWords = 256;
+// Words of the look over a float64 Gaussian fit's inputs: a count of finished
+// blocks (zero between the calls), its result, and each block's part, two
+// words per attribute.  Fits of few values need none (their tiles look for
+// themselves).
+constexpr int kF64LookBlocks = 64;
+constexpr int kF64MaxAttrs = 255;
+constexpr int kF64Words = 2 + kF64LookBlocks * 2 * kF64MaxAttrs;
+bool f64_needs_words(int64_t n, int32_t D);
 // Scratch that the library states for a float64 Gaussian fit: 8 bytes per
 // point (padded to 64) and grid column or row (padded to 16), none past the
 // cap.  The fit itself needs none of it since its tiles form their own
