@@ -45,8 +45,8 @@ struct mls_context {
   Scratch scratch;
   // fit staging: attribute ranges, shift/scale, normalised values
   Scratch fit_scratch;
-  // words of the float64 fit's look over its inputs (mls_internal.h), for the
-  // context's lifetime
+  // words of the float64 fit's look over its inputs (mls_internal.h), from the
+  // first call that needs them or mls_context_reserve on
   uint32_t* words = nullptr;
 
   // pinned host word for counts read back by mls_contour
@@ -417,16 +417,9 @@ mls_status mls_context_create(int32_t device, mls_context** out) {
     delete ctx;
     return device_fail(e, "hipEventCreateWithFlags");
   }
-  const mls_status st = ensure_words(ctx);
-  if (st != MLS_OK) {
-    (void)hipEventDestroy(ctx->last_use);
-    delete ctx;
-    return st;
-  }
   // the fixed scratch of mls_contour_static: its address on this device
   e = mls::contour_static_scratch_resolve(device);
   if (e != hipSuccess) {
-    (void)hipFree(ctx->words);
     (void)hipEventDestroy(ctx->last_use);
     delete ctx;
     return device_fail(e, "hipGetSymbolAddress (contour scratch)");
@@ -640,7 +633,12 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
     if (weight->kind == MLS_W_INVPOW &&
         (st = ensure_scratch(ctx->fit_scratch, plan.total)) != MLS_OK)
       return st;
-    if ((st = scratch_acquire(ctx, s)) != MLS_OK) return st;
+    // a Gaussian fit that shares nothing with other calls is not ordered
+    // after them
+    const bool words = weight->kind == MLS_W_GAUSSIAN && mls::f64_needs_words(n, d);
+    const bool shared = words || weight->kind == MLS_W_INVPOW;
+    if (words && (st = ensure_words(ctx)) != MLS_OK) return st;
+    if (shared && (st = scratch_acquire(ctx, s)) != MLS_OK) return st;
     a.words = ctx->words;
     e = mls::launch_fit_f64(a, s);
     if (e != hipSuccess) return device_fail(e, "fit kernel launch");
@@ -673,7 +671,7 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
       tr.mark("hits");
     }
     tr.finish();
-    return scratch_release(ctx, s);
+    return shared ? scratch_release(ctx, s) : MLS_OK;
   }
   const bool fp16 = precision == MLS_PREC_FP16;
   const mls::FitPlan plan = mls::make_fit_plan(n, d, precision, weight->kind, weight->h,
@@ -948,7 +946,8 @@ mls_status mls_context_reserve(mls_context* ctx, size_t bytes) {
   if (!ctx) return fail(MLS_ERR_INVALID_ARG, "ctx is NULL");
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return device_fail(e, "hipSetDevice");
-  return ensure_scratch(ctx->fit_scratch, bytes);
+  const mls_status st = ensure_words(ctx);
+  return st == MLS_OK ? ensure_scratch(ctx->fit_scratch, bytes) : st;
 }
 
 mls_status mls_fit(mls_context* ctx, const float* d_points, const float* d_values,
