@@ -95,6 +95,11 @@ typedef enum {
  *  MLS_PREC_FP16: the same with float16 terms (default 2 terms, about 22
  *                 bits; 3 products per feature).  Weights are scaled by
  *                 2^15 internally to stay above float16's subnormals.
+ * That is the one-pass form.  In two passes (mls_solve_opts.lp_form) the
+ * moments are carried like that; the fields are then sums of effective weights
+ * (the weight times the node's shape function, formed per pair in float32 and
+ * carried as hi + lo; float16 first rounds the weight to the digits that the
+ * moments saw) times attributes carried as two terms, accumulated in float32.
  */
 typedef enum {
   MLS_PREC_F64 = 0,
@@ -133,7 +138,9 @@ typedef struct {
                            2 = two passes (shape-function form: the moments
                            and each node's ladder first, then the effective
                            weights w (y^T b) against the attributes, F =
-                           n_mom + D columns).  Ignored elsewhere */
+                           n_mom + D columns).  Ignored elsewhere, and with
+                           MLS_PREC_FP16 and lp_terms = 3 (one pass, all
+                           three terms of every attribute) */
 } mls_solve_opts;
 
 typedef struct mls_context mls_context;

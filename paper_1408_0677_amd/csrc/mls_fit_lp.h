@@ -890,13 +890,18 @@ __global__ __launch_bounds__(kThreads) void fit_lp_kernel(LPParams p) {
 // attribute slab instead of per feature.  The error stays the float32
 // accumulation of the moments in pass 1: the effective weights and the
 // attribute terms add about 2^-16 (bfloat16) or 2^-22 (float16) relative per
-// pair, which is not amplified by the conditioning.
+// pair, which is not amplified by the conditioning, and float16 weighs a pair
+// in both passes by the same rounded weight (pair_weight).
 //
 // float16 needs its range looked after.  The weights carry their gain 2^15
 // into pass 1, which leaves y_p 2^-15 of its size.  An effective weight is at
-// most sum_j |z_j| (z the node-frame coefficients, since |b_j(u)| exp(-u^2)
-// <= 1), so each node's y_p is scaled by the power of two that brings this
-// bound to 2^14 .. 2^15 (shape_scale); the attributes are scaled by 2^10 so
+// most sum_j |z_j| c_j, z the node-frame coefficients and c_j the largest |b_j(u)|
+// exp(-u^2) of a point that weighs no more than the node's weight sum (at most
+// 1), so each node's y_p is scaled by the power of two that brings this bound
+// to 2^14 .. 2^15 (shape_scale).  With c_j = 1, the effective weights of nodes
+// that only far points determine were as small as the sum below that and lost
+// their digits: at sums of 1e-6 to 1e-5 the linear basis with 48 attributes was
+// off by 8.1e-4 rms, where one pass is off by 1.2e-4.  The attributes are scaled by 2^10 so
 // that the second term of a value near 0 keeps its digits.  The node's power
 // and the 2^10 are taken out of the float32 sum at the end, exactly.
 //
@@ -1127,6 +1132,18 @@ __device__ __forceinline__ void shape_chunk(const LPParams& p, const float* raw,
   }
 }
 
+// A pair's weight as pass 1 saw it.  Its hi + lo terms in float16 end at 2^-24,
+// the format's smallest number, and the moments and the products have to see
+// the same weight (the top of this file), so it is rounded to that here as
+// well: below 0.5 the sum with 0.5 ends at 2^-24, above it at about the digits
+// of hi + lo.  One instruction per pair: 7,351 points, 19 attributes,
+// 701 x 643 545 -> 548 us.
+template <typename T>
+__device__ __forceinline__ float pair_weight(float gx, float gy) {
+  if constexpr (__is_same(T, _Float16)) return fmaf(gx, gy, 0.5f) - 0.5f;
+  return gx * gy;
+}
+
 // The power of two that brings an effective weight's bound, `b`, to 2^14 ..
 // 2^15 (float16; at most 2^+-100), 1 for bfloat16.
 template <typename T>
@@ -1334,10 +1351,17 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
       low = ADAPT && in && code != 255 && lad.diag < (double)(scale * kDiagFloor);
       float g = 1.0f;
       if (__is_same(T, _Float16) && code != 255) {
-        double b = 0.0;   // z = S w in the node's frame, times the weights' gain
+        // z = S w in the node's frame, times the weights' gain.  No point weighs
+        // more than the sum, so for sums below 1/e the largest |b_j| exp(-u^2)
+        // is that at u^2 = -ln sum
+        const float sum = e[0] * (1.0f / WeightGain<T>::value);
+        const float u2 = fmaxf(1.0f, -__logf(sum)), most = fminf(1.0f, sum * 1.01f);
+        double b = 0.0;
 #pragma unroll
-        for (int j = 0; j < m; ++j)
-          if (j < lad.mk) b += fabs(lad.s[j] * lad.w[j]);
+        for (int j = 0; j < m; ++j) {
+          const float size = j == 0 ? 1.0f : (j < 3 ? __builtin_amdgcn_sqrtf(u2) : u2);
+          if (j < lad.mk) b += fabs(lad.s[j] * lad.w[j]) * (double)fminf(1.0f, most * size);
+        }
         g = shape_scale<T>(b * (double)WeightGain<T>::value);
       }
       float* yv = ybuf + (row * kCols + col) * m;
@@ -1415,7 +1439,7 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
                   const float s2 = fmaf(yv[t][5], b2, yv[t][2]);
                   sh = fmaf(b1, s1, fmaf(b2, s2, yv[t][0]));
                 }
-                w[t][e] = (wxq * gy[(wave * R + t) * KSF + k]) * sh;
+                w[t][e] = pair_weight<T>(wxq, gy[(wave * R + t) * KSF + k]) * sh;
               }
             }
 #pragma unroll

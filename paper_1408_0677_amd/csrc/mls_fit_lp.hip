@@ -167,6 +167,10 @@ double lp_tile_extent(double dx, double dy, double h) {
 bool lp_use_shape_form(int degree, int D, bool fp16, int wkind, bool grads, int terms,
                        int forced_ds, int form) {
   if (wkind != 0 || grads || degree < 1) return false;
+  // two passes carry an attribute in two terms, which float16 callers can ask
+  // more than (bfloat16's default is three, and two passes its plan since they
+  // exist)
+  if (fp16 && terms > kShapeS2) return false;
   if (form == 1) return false;
   if (form == 2) return true;
   // The library's choice.  Two passes list once and contract twice; each has
