@@ -92,8 +92,12 @@ __device__ __forceinline__ double invpow_weight(double r2, double alpha) {
 }
 
 // Smallest squared offset along x: a node on a point (r^2 = 0) gets a large
-// finite weight; such nodes are overwritten by the exact-hit pass.
-constexpr double kMinOffset2 = 0x1p-126;
+// finite weight; such nodes are overwritten by the exact-hit pass.  Far below
+// any other pair's r^2, also where h is a unit many times the points' distances
+// (a pair 1e-9 apart has r^2 = 1e-58 with h = 1e20), and such that its square's
+// reciprocal times the features stays finite.
+template <int WM>
+constexpr double kMinOffset2 = WM == WM_INV2 ? 1e-140 : 1e-300;
 
 // The same weight for alpha = 1 and alpha = 2: the hardware's float64
 // reciprocal estimate (relative error at most 4.5e-8, 1.0e-8 rms over
@@ -261,7 +265,7 @@ void fit_f64_kernel(F64Params p) {
       const double u = xaxis ? ux[k] : uy[k];
       for (int c = 0; c < mid; ++c) {
         const double o = u - (double)(c - (up ? 0 : mid)) * s;
-        g[c * KS] = k < kn ? fma(o, o, xaxis ? kMinOffset2 : 0.0) : __builtin_inf();
+        g[c * KS] = k < kn ? fma(o, o, xaxis ? kMinOffset2<WM> : 0.0) : __builtin_inf();
       }
     }
     // 2b. moment monomials of the tile-frame coordinates
