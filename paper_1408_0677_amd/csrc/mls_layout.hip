@@ -56,6 +56,7 @@ struct LayoutParams {
   const int32_t* fan;
   int64_t n_fan;                // triangles in fan (pairs)
   double C, D, eta, t;
+  double r2_min;                // repulsion_factor
 };
 
 // Entries [start[v], start[v+1]) of a CSR list, clipped to [0, total): the
@@ -143,10 +144,11 @@ __device__ __forceinline__ double triangle_scale(double vx, double vy, double ax
 // residual step on the quotient: within about 1e-14 of the correctly
 // rounded value, in about half the instructions of the IEEE square root and
 // division, and without a branch.  V = 0 (the node itself, or a coincident
-// node) takes |V| = 1e-150 so that the factor stays finite and its product
-// with V is exactly zero.
-__device__ __forceinline__ double repulsion_factor(double r2, double C, double eta) {
-  const double a = fmax(r2, 1e-300);
+// node) takes |V|^2 = r2_min so that the factor stays finite, whatever eta is,
+// and its product with V is exactly zero.
+__device__ __forceinline__ double repulsion_factor(double r2, double C, double eta,
+                                                   double r2_min) {
+  const double a = fmax(r2, r2_min);
   const double y = __builtin_amdgcn_rsq(a);
   const double g = a * y;
   const double L = fma(g, fma(-g, 0.5 * y, 0.5), g);   // g (3 - a y^2) / 2
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(kLanes) void layout_step_kernel(LayoutParams p) {
     for (int e = s; e < cnt; e += SP) {
       const double2 q2 = src[e];
       const double ax = vx - q2.x, ay = vy - q2.y;
-      const double q = repulsion_factor(fma(ay, ay, ax * ax), p.C, p.eta);
+      const double q = repulsion_factor(fma(ay, ay, ax * ax), p.C, p.eta, p.r2_min);
       fx = fma(q, ax, fx);
       fy = fma(q, ay, fy);
     }
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(kLanes) void layout_group_kernel(LayoutParams p) {
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         const double ax = nx[b] - cur[i].x, ay = ny[b] - cur[i].y;
-        const double q = repulsion_factor(fma(ay, ay, ax * ax), C, p.eta);
+        const double q = repulsion_factor(fma(ay, ay, ax * ax), C, p.eta, p.r2_min);
         fx[b] = fma(q, ax, fx[b]);
         fy[b] = fma(q, ay, fy[b]);
       }
@@ -494,6 +496,9 @@ hipError_t launch_layout(const LayoutArgs& a, hipStream_t s) {
   p.C = a.C;
   p.D = a.D;
   p.eta = a.eta;
+  // |V|^3 of at least 1e-300 and 1e-300 C: float32 coordinates are not as close
+  // as that for C up to 1e160
+  p.r2_min = fmax(1e-200, pow(a.C * 1e-300, 2.0 / 3.0));
   double* cur = a.buf0;
   double* nxt = a.buf1;
   double t = a.t0;
