@@ -45,7 +45,7 @@ struct F64Params {
   // the attributes' sizes (look_kernel; null: the tiles look themselves)
   double list_log;     // ln n + 54 ln 2, or infinite: every tile sums all points
   const uint32_t* sizes;
-  bool vec4;           // rows of the fields are 16-byte aligned
+  bool vec4;           // rows of the fields and of the slopes are 16-byte aligned
   bool fine;           // a tile spans at most kFineSpan h on either axis
 };
 

@@ -603,7 +603,7 @@ hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream) {
   hipError_t e;
   p.list_log = a.n <= kReachPoints ? log((double)a.n) + 54.0 * 0.6931471805599453 : HUGE_VAL;
   p.sizes = nullptr;
-  p.vec4 = (a.W & 3) == 0 && ((uintptr_t)a.fields & 15) == 0;
+  p.vec4 = (a.W & 3) == 0 && (((uintptr_t)a.fields | (uintptr_t)a.grads) & 15) == 0;
   if (f64_needs_words(a.n, a.D)) {
     const int64_t nb = (a.n * a.D + 1023) / 1024;
     p.sizes = a.words + 1;
