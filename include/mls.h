@@ -203,9 +203,12 @@ void mls_context_destroy(mls_context* ctx);
  * takes the mean of their values, degree code 254; library scratch of about
  * 16 n bytes).  Other combinations return MLS_ERR_UNSUPPORTED.  Gaussian
  * fits sum, per tile of nodes, the points whose weight can matter at the
- * precision's own rounding (all points with MLS_PREC_F64 and n > 32768, with
- * a weight_floor of 0 where no point is near, or with inputs that are not
- * finite).  The 16-bit precisions
+ * precision's own rounding; with MLS_PREC_F64 an attribute whose values differ
+ * by more than 2^24 in size widens that by the rest, so that a far point's large
+ * value is not lost, and with the 16-bit precisions it is the weight alone, in
+ * units of the attribute's range.  (All points with MLS_PREC_F64 and n > 32768,
+ * with a weight_floor of 0 where no point is near, or with inputs that are not
+ * finite.)  The 16-bit precisions
  * also return MLS_ERR_UNSUPPORTED when a node tile spans more than
  * MLS_LP_MAX_TILE_SPAN_<basis> (linear, quadratic), and MLS_PREC_FP16 when
  * tile-frame features would leave the float16 range; MLS_PREC_F64 serves
@@ -305,10 +308,12 @@ mls_status mls_context_trace_last(mls_context* ctx, mls_trace_record* out);
 
 /*
  * Device scratch bytes mls_fit needs for this request; 0 also for invalid
- * arguments.  For MLS_PREC_F64 with the Gaussian weight it states
+ * arguments.  For MLS_PREC_F64 with the Gaussian weight it is at most
  * 8 x (n rounded up to 64) x (width and height each rounded up to 16) bytes
- * when that is at most 512 MiB, else 0; the fit itself allocates none of it.
- * The inverse-distance weight needs about 16 n bytes.
+ * when that is at most 512 MiB, else 0: the weight factors of every grid column
+ * and row, which fits over all points in one pass tabulate (fits over the
+ * points in reach need none).  The inverse-distance weight needs about 16 n
+ * bytes.
  */
 size_t mls_fit_scratch_bytes(int64_t n, int32_t d, int32_t precision,
                              const mls_weight* weight, const mls_grid* grid);

@@ -295,8 +295,11 @@ FitPlan make_fit_plan(int64_t n, int32_t d, int32_t precision, int32_t wkind, do
     return o;
   };
   if (precision == MLS_PREC_F64) {
-    // stated, not used (f64_scratch_bytes)
-    if (wkind == MLS_W_GAUSSIAN) carve(f64_scratch_bytes(n, W, H));
+    // the Gaussian's factor tables, for the fits that sum all points
+    if (wkind == MLS_W_GAUSSIAN) {
+      p.table_bytes = f64_table_bytes(n, W, H);
+      p.o_table = carve(p.table_bytes);
+    }
     // the inverse-distance weight's exact-hit pass sorts (node, point) keys
     if (wkind == MLS_W_INVPOW) {
       p.o_keys = carve(4 * (size_t)n);
@@ -585,6 +588,7 @@ mls_status fit_prepare(mls_context* ctx, const float* d_points, const float* d_v
   a.grads = d_grad;
   a.lp_form = form;
   a.words = nullptr;
+  a.table = nullptr;
   *out = a;
   *terms_out = terms;
   return MLS_OK;
@@ -630,16 +634,16 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
     const mls::FitPlan plan = mls::make_fit_plan(n, d, precision, weight->kind, weight->h,
                                                  grid->x0, grid->y0, grid->dx, grid->dy,
                                                  grid->width, grid->height);
-    if (weight->kind == MLS_W_INVPOW &&
-        (st = ensure_scratch(ctx->fit_scratch, plan.total)) != MLS_OK)
-      return st;
+    const bool table = mls::f64_sums_all(a) && plan.table_bytes > 0;
+    const bool words = mls::f64_needs_words(a);
     // a Gaussian fit that shares nothing with other calls is not ordered
     // after them
-    const bool words = weight->kind == MLS_W_GAUSSIAN && mls::f64_needs_words(n, d);
-    const bool shared = words || weight->kind == MLS_W_INVPOW;
+    const bool scratch = table || weight->kind == MLS_W_INVPOW;
+    if (scratch && (st = ensure_scratch(ctx->fit_scratch, plan.total)) != MLS_OK) return st;
     if (words && (st = ensure_words(ctx)) != MLS_OK) return st;
-    if (shared && (st = scratch_acquire(ctx, s)) != MLS_OK) return st;
+    if ((scratch || words) && (st = scratch_acquire(ctx, s)) != MLS_OK) return st;
     a.words = ctx->words;
+    if (table) a.table = (double*)((char*)ctx->fit_scratch.ptr + plan.o_table);
     e = mls::launch_fit_f64(a, s);
     if (e != hipSuccess) return device_fail(e, "fit kernel launch");
     tr.set_form(0);
@@ -671,7 +675,7 @@ static mls_status fit_impl(mls_context* ctx, const float* d_points, const float*
       tr.mark("hits");
     }
     tr.finish();
-    return shared ? scratch_release(ctx, s) : MLS_OK;
+    return scratch || words ? scratch_release(ctx, s) : MLS_OK;
   }
   const bool fp16 = precision == MLS_PREC_FP16;
   const mls::FitPlan plan = mls::make_fit_plan(n, d, precision, weight->kind, weight->h,

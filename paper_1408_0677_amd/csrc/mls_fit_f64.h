@@ -34,6 +34,10 @@ struct F64Params {
   int D, F;
   double h, inv_h;
   double alpha;        // inverse-distance exponent (WM_INV kernels)
+  // Gaussian over all points, WM_TABLE: factors of every grid column and row
+  const double* tab;   // rows [0, tab_cols) the columns, then the grid's rows
+  int64_t tab_n;       // points per row
+  int tab_cols;
   double x0, y0, dx, dy;
   int W, H, tiles_x;
   double tau, floor_w;
@@ -52,9 +56,15 @@ struct F64Params {
 constexpr double kFineSpan = 8.0;
 constexpr double kFineReach2 = 18.0 * 18.0;
 
-// Weight modes of the kernel: the Gaussian, the inverse-distance weight per
-// pair (any exponent, or alpha = 1 and alpha = 2 through a reciprocal).
-constexpr int WM_GAUSS = 0, WM_INV = 1, WM_INV1 = 2, WM_INV2 = 3;
+// Weight modes of the kernel: the Gaussian over the points in reach, the
+// inverse-distance weight per pair (any exponent, or alpha = 1 and alpha = 2
+// through a reciprocal), the Gaussian over all points with factors from tables
+// of the launch or formed by the tile.
+constexpr int WM_GAUSS = 0, WM_INV = 1, WM_INV1 = 2, WM_INV2 = 3, WM_TABLE = 4, WM_STEP = 5;
+
+// One-pass fits by source file (mls_fit_f64_kernel.h).
+hipError_t launch_fit_f64_inv(const F64Params& p, int degree, int nt, hipStream_t s);
+hipError_t launch_fit_f64_all(const F64Params& p, int degree, int nt, double* tab, hipStream_t s);
 
 // Two-pass form of the Gaussian fit (mls_fit_f64_shape.hip).
 hipError_t launch_fit_f64_shape(const F64Params& p, int degree, hipStream_t s);
@@ -186,8 +196,10 @@ __device__ __forceinline__ void look_sizes(const float* vals, int64_t n, int D, 
 // The reach of the tile whose anchor node is (c0 + 8, r0 + rows / 2).  Every
 // thread of the workgroup calls it; `shared` is LDS for kWaves floats and 2 D
 // words, and the call ends with a barrier.  S is the sum over the points of
-// the weight at their farthest node of the tile; below 1,024 points, where a
+// the weight at their farthest node of the tile; below kFloorPoints, where a
 // pass over them costs as much as it saves, S = 0.
+constexpr int kFloorPoints = 1024;
+
 template <int DEG>
 __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, double cx, double cy,
                                                float* shared) {
@@ -215,7 +227,7 @@ __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, dou
   }
   const auto pts = global_ptr(p.pts);
   float S = 0.0f;
-  if (p.n >= 1024) {
+  if (p.n >= kFloorPoints) {
 #pragma unroll 4
     for (int i = tid; i < (int)p.n; i += kThreads) {
       const float ax = (float)(fabs(fma((double)pts[2 * i], p.inv_h, -t.ox)) + t.ex);

@@ -28,6 +28,7 @@ struct FitArgs {
   float* grads;         // [D][2][H][W] slopes of the local fits, or null
   bool rigid;           // rigid map of 2-vector values (degree 1 moments, D = 2)
   uint32_t* words;      // float64 Gaussian, f64_needs_words: kF64Words of the context
+  double* table;        // float64 Gaussian, f64_sums_all: f64_table_bytes of scratch, or null
 };
 
 // Number of basis terms m and of distinct moment monomials for a degree.
@@ -44,13 +45,14 @@ hipError_t launch_fit_f64(const FitArgs& a, hipStream_t stream);
 constexpr int kF64LookBlocks = 64;
 constexpr int kF64MaxAttrs = 255;
 constexpr int kF64Words = 2 + kF64LookBlocks * 2 * kF64MaxAttrs;
-bool f64_needs_words(int64_t n, int32_t D);
-// Scratch that the library states for a float64 Gaussian fit: 8 bytes per
-// point (padded to 64) and grid column or row (padded to 16), none past the
-// cap.  The fit itself needs none of it since its tiles form their own
-// factors; slots and budgets sized by the figure stay valid.
-constexpr size_t kF64ScratchCap = (size_t)512 << 20;
-size_t f64_scratch_bytes(int64_t n, int32_t W, int32_t H);
+bool f64_needs_words(const FitArgs& a);
+// Whether a float64 Gaussian fit sums all points in one pass, for which it
+// tabulates the weight factors of every grid column and row (points padded to
+// the chunk, columns and rows to the tile) where that passes no more than the
+// cap (0 bytes: the tiles form them).
+bool f64_sums_all(const FitArgs& a);
+constexpr size_t kF64TableCap = (size_t)512 << 20;
+size_t f64_table_bytes(int64_t n, int32_t W, int32_t H);
 
 // Cell-ordered payload for compactly supported weights (from launch_cells).
 struct CellGeom;
@@ -220,6 +222,7 @@ struct FitPlan {
   size_t o_keys, o_keys2, o_perm, o_perm2, o_hist, o_cs, o_pts, o_vals_s;
   size_t o_tk, o_tk2, o_to, o_to2, o_th;
   size_t o_ts, o_tl, o_so, o_ssum;
+  size_t o_table, table_bytes;   // float64 Gaussian factor tables (f64_sums_all)
   int64_t order_slots;
   int64_t list_cap;       // entries of the per-tile point lists, at most
   size_t total;
