@@ -69,15 +69,36 @@ hipError_t launch_fit_f64_all(const F64Params& p, int degree, int nt, double* ta
 // Two-pass form of the Gaussian fit (mls_fit_f64_shape.hip).
 hipError_t launch_fit_f64_shape(const F64Params& p, int degree, hipStream_t s);
 bool f64_use_shape_form(int degree, int D);
-// Strips of 16 nodes per wave (1, 2 or 4; a tile is 16 x 4 R nodes): the
-// largest that leaves kF64Tiles workgroups, about four per compute unit.
-constexpr int64_t kF64Tiles = 1024;
-inline int f64_tile_strips(int W, int H, int most) {
-  int R = most;
-  while (R > 1 && (int64_t)((W + kCols - 1) / kCols) *
-                          ((H + kWaves * R - 1) / (kWaves * R)) < kF64Tiles)
-    R /= 2;
-  return R;
+// Matrix and weight cycles of one strip's 64 node-point pairs: 64 per 16 columns
+// (17 per 4 with the four-block form, up to 12), 4 for a weight.
+inline int f64_pair_cycles(int columns, bool blocks4) {
+  return 4 + (blocks4 && columns <= 12 ? 17 * ((columns + 3) / 4) : 64 * ((columns + 15) / 16));
+}
+// Strips of 16 nodes per wave (1, 2 or 4, at most `most`; a tile is 16 x 4 R
+// nodes).  A chunk costs a workgroup its production, whatever R, and the sweep of
+// R strips, whose `cycles` count per 64 pairs over its `passes`; the fullest
+// compute unit decides, and where it holds one workgroup, the waits between the
+// two are not covered either.  Over 390 calls (200 to 30,000 points, 128^2 to
+// 1024^2, every form) the choice was within 0.2% of the best on average and 16%
+// at worst.  (Taking the largest R that leaves 1,024 workgroups, whatever the
+// chunks cost, was 10% slower on average and twice as slow where a tile's list
+// is long: 30,000 points, all in reach, 256^2, one attribute 1,591 us with R = 1,
+// 1,043 with R = 2.)
+inline int f64_tile_strips(int W, int H, int most, int passes, int cycles) {
+  int best = most;
+  int64_t least = 0;
+  for (int R = most; R >= 1; R /= 2) {
+    const int64_t tiles =
+        (int64_t)((W + kCols - 1) / kCols) * ((H + kWaves * R - 1) / (kWaves * R));
+    const int64_t per_unit = (tiles + 255) / 256;
+    const int64_t cost =
+        per_unit * (600 * passes + 16 * R * cycles) + (per_unit == 1 ? 1500 * passes : 0);
+    if (R == most || cost < least) {
+      best = R;
+      least = cost;
+    }
+  }
+  return best;
 }
 
 namespace {

@@ -449,13 +449,12 @@ hipError_t launch_impl(const F64Params& prm, hipStream_t s) {
   return hipGetLastError();
 }
 
-// R (row strips per wave) trades accumulator registers against the number
-// of weight factors per tile.  With one feature tile, where registers allow
-// any R, small grids take fewer strips so that their tiles fill the chip.
+// R (row strips per wave): with one feature tile, where registers allow any,
+// what the grid and the sweep make best (f64_tile_strips).
 template <int DEG, int NT, int WM, int EPI, int Q4>
 hipError_t launch_strips(const F64Params& p, hipStream_t s) {
   if constexpr (NT == 1) {
-    switch (f64_tile_strips(p.W, p.H, 4)) {
+    switch (f64_tile_strips(p.W, p.H, 4, 1, f64_pair_cycles(p.F, Q4 > 0))) {
       case 1: return launch_impl<DEG, NT, 1, WM, EPI, Q4>(p, s);
       case 2: return launch_impl<DEG, NT, 2, WM, EPI, Q4>(p, s);
       default: return launch_impl<DEG, NT, 4, WM, EPI, Q4>(p, s);

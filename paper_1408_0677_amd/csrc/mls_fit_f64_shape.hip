@@ -419,7 +419,12 @@ hipError_t launch_impl(const F64Params& prm, hipStream_t s) {
 
 template <int DEG, int NT, int QD, int NE>
 hipError_t launch_tiles(const F64Params& p, hipStream_t s) {
-  switch (f64_tile_strips(p.W, p.H, DEG == 1 ? 4 : 2)) {
+  // (the slopes do not enter: the tiles' frames are those of a call without, and
+  // so are the fields' bits)
+  const int attrs = p.D < 48 ? p.D : 48;
+  const int cycles = f64_pair_cycles(moment_terms(DEG), DEG == 1) +
+                     f64_pair_cycles(attrs, true) + (DEG == 1 ? 12 : 24);
+  switch (f64_tile_strips(p.W, p.H, DEG == 1 ? 4 : 2, 2, cycles)) {
     case 1: return launch_impl<DEG, NT, QD, 1, NE>(p, s);
     case 2: return launch_impl<DEG, NT, QD, 2, NE>(p, s);
     default:
