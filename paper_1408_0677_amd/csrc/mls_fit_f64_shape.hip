@@ -25,7 +25,7 @@
 // of which the reach gives 6.1x and the rest is this form.  Counters there:
 // matrix instructions busy 49% and vector instructions 24% of the SIMDs'
 // cycles, 35.4M matrix instructions.  3,001 points, 5 attributes, quadratic,
-// 517 x 389, with slopes: 1,500 -> 930 us.
+// 517 x 389, with slopes: 1,500 -> 854 us (930 with a sweep for each output).
 #include "mls_fit_f64.h"
 
 namespace mls {
@@ -233,15 +233,21 @@ void fit_f64_shape_kernel(F64Params p) {
   const int i = lane & 15;
   const int ci = QD > 0 ? i : 4 * (i & 3) + (i >> 2);
   const int kq = (lane >> 4) * 4;
-  double yv[R][m];
-  auto load_y = [&](int e) {
+  // Slopes: the three outputs share a sweep's loads and weights (EF = 3; 5,000
+  // points, 8 attributes, 1024^2 2,044 -> 1,938 us, quadratic with 4 2,707 ->
+  // 2,491) unless their accumulators and coefficients pass the registers.
+  constexpr int EF = NE > 1 && DEG == 1 && R == 4 && (QD == 0 || QD == 3) ? 1 : NE;
+  double yv[EF][R][m];
+  auto load_y = [&](int e0) {
 #pragma unroll
-    for (int t = 0; t < R; ++t)
+    for (int e = 0; e < EF; ++e)
 #pragma unroll
-      for (int j = 0; j < m; ++j)
-        yv[t][j] = ybuf[((wave * R + t) * kCols + ci) * L::kYStride + e * m + j];
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int j = 0; j < m; ++j)
+          yv[e][t][j] = ybuf[((wave * R + t) * kCols + ci) * L::kYStride + (e0 + e) * m + j];
   };
-  if (NE == 1) load_y(0);
+  if (EF == NE) load_y(0);
   for (int d0 = 0; d0 < D; d0 += L::kFP2) {
     const int nv = D - d0 < L::kFP2 ? D - d0 : L::kFP2;
     // element e = tid + it kThreads of a chunk's values: point e / nv
@@ -306,8 +312,8 @@ void fit_f64_shape_kernel(F64Params p) {
         prefetch_values((c + 1) * KT);
         __syncthreads();
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-        if (NE > 1) load_y(e);
+        for (int e0 = 0; e0 < NE; e0 += EF) {
+        if (EF < NE) load_y(e0);
 #pragma unroll 1
         for (int kg = 0; kg < KT; kg += 16) {
           double ax[4], ay[R][4], bx[4], by[4], bv[QD > 0 ? QD : NT][4];
@@ -327,25 +333,30 @@ void fit_f64_shape_kernel(F64Params p) {
           for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int t = 0; t < R; ++t) {
-              double sh;
-              if constexpr (DEG == 1) {
-                sh = fma(yv[t][2], by[j], fma(yv[t][1], bx[j], yv[t][0]));
-              } else {
-                const double s1 = fma(yv[t][3], bx[j], fma(yv[t][4], by[j], yv[t][1]));
-                const double s2 = fma(yv[t][5], by[j], yv[t][2]);
-                sh = fma(bx[j], s1, fma(by[j], s2, yv[t][0]));
-              }
-              const double a = (ax[j] * ay[t][j]) * sh;
-              if constexpr (QD > 0) {
+              const double w = ax[j] * ay[t][j];
 #pragma unroll
-                for (int q = 0; q < QD; ++q)
-                  acc4[e][t][q] =
-                      __builtin_amdgcn_mfma_f64_4x4x4f64(a, bv[q][j], acc4[e][t][q], 0, 0, 0);
-              } else {
+              for (int e = 0; e < EF; ++e) {
+                const double* y = yv[e][t];
+                double sh;
+                if constexpr (DEG == 1) {
+                  sh = fma(y[2], by[j], fma(y[1], bx[j], y[0]));
+                } else {
+                  const double s1 = fma(y[3], bx[j], fma(y[4], by[j], y[1]));
+                  const double s2 = fma(y[5], by[j], y[2]);
+                  sh = fma(bx[j], s1, fma(by[j], s2, y[0]));
+                }
+                const double a = w * sh;
+                if constexpr (QD > 0) {
 #pragma unroll
-                for (int q = 0; q < NT; ++q)
-                  acc[e][t][q] =
-                      __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv[q][j], acc[e][t][q], 0, 0, 0);
+                  for (int q = 0; q < QD; ++q)
+                    acc4[e0 + e][t][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(
+                        a, bv[q][j], acc4[e0 + e][t][q], 0, 0, 0);
+                } else {
+#pragma unroll
+                  for (int q = 0; q < NT; ++q)
+                    acc[e0 + e][t][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        a, bv[q][j], acc[e0 + e][t][q], 0, 0, 0);
+                }
               }
             }
         }
