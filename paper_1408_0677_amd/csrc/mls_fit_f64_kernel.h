@@ -101,7 +101,7 @@ __device__ __forceinline__ double invpow_weight_int(double r2) {
 // three short instructions where the 16x16x4 one carries 4 to 13 empty
 // columns.
 template <int DEG, int NT, int R, int WM, int EPI, int Q4 = 0>
-__global__ __launch_bounds__(kThreads, WM == WM_GAUSS ? (NT == 1 ? 3 : 2) : 1)
+__global__ __launch_bounds__(kThreads, WM == WM_GAUSS && NT <= 4 ? (NT == 1 ? 3 : 2) : 1)
 void fit_f64_kernel(F64Params p) {
   static_assert(Q4 == 0 || NT == 1, "the 4x4x4 form covers one feature tile");
   constexpr bool INV = WM == WM_INV || WM == WM_INV1 || WM == WM_INV2;
