@@ -189,27 +189,27 @@ __device__ __forceinline__ bool in_reach(const F64Reach& t, float x, float y) {
   return !(ax * ax + ay * ay > t.r2);
 }
 
-// The look over n x D values by the workgroup's threads (the first
-// threads / D * D of them: each keeps to one attribute), into LDS words hi[D]
-// and lo[D], which the caller has set to 0 and 0x7F800000 before a barrier and
+// The look over n x D values by the workgroup's T threads (the first T / D * D
+// of them: each keeps to one attribute), into LDS words hi[D] and lo[D], which the caller has set to 0 and 0x7F800000 before a barrier and
 // reads after one.  A coordinate that is not finite counts as an attribute 0
 // that is not.  Elements are taken from block `b` of `nb`.
+template <int T>
 __device__ __forceinline__ void look_sizes(const float* vals, int64_t n, int D, const float* pts,
                                            int b, int nb, uint32_t* hi, uint32_t* lo) {
   const auto v = global_ptr(vals);
   const auto q = global_ptr(pts);
-  const int tid = threadIdx.x, per = kThreads / D * D;
+  const int tid = threadIdx.x, per = T / D * D;
   Sizes sz;
   if (tid < per) {
     const int64_t step = (int64_t)nb * per, total = n * D;
-#pragma unroll 4
+#pragma unroll 8
     for (int64_t e = (int64_t)b * per + tid; e < total; e += step) sz.add(v[e]);
     atomicMax(hi + tid % D, sz.hi);
     atomicMin(lo + tid % D, sz.lo);
   }
   bool bad = false;
 #pragma unroll 4
-  for (int64_t e = (int64_t)b * kThreads + tid; e < 2 * n; e += (int64_t)nb * kThreads)
+  for (int64_t e = (int64_t)b * T + tid; e < 2 * n; e += (int64_t)nb * T)
     bad |= !(fabsf(q[e]) < __builtin_inff());
   if (bad) atomicMax(hi, 0x7F800000u);
 }
@@ -258,7 +258,7 @@ __device__ __forceinline__ F64Reach tile_reach(const F64Params& p, int rows, dou
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
   }
-  if (!p.sizes) look_sizes(p.vals, p.n, D, p.pts, 0, 1, hi, lo);
+  if (!p.sizes) look_sizes<kThreads>(p.vals, p.n, D, p.pts, 0, 1, hi, lo);
   if (lane == 0) shared[wave] = S;
   __syncthreads();
   S = 0.0f;
