@@ -445,18 +445,17 @@ mls_status mls_map_adaptive(mls_context* ctx, const float* d_fields, const float
  * requests as they arrive, on `slots` execution slots (a stream and a
  * context with reserved scratch each).  Whenever a slot is free, a
  * scheduler thread gives it the request at the head of the queue together
- * with the later queued requests of the same kernel class (16-bit one-pass
- * fits with the Gaussian weight, no gradients and the format's default
- * lp_terms, of one degree, feature tiles per workgroup and format), in
- * arrival order, while their
- * staging fits the slot's scratch.  Such a batch runs as one persistent
+ * with the later queued requests of the same kernel class (16-bit fits with
+ * the Gaussian weight, no gradients and the format's default lp_terms, of one
+ * degree, form, feature tiles per workgroup and format), in arrival order,
+ * while their staging fits the slot's scratch.  Such a batch runs as one persistent
  * kernel whose workgroups take (request, tile) work items from a device
  * counter; each request's completion flag lives in pinned host memory and
  * is set by the workgroup that finishes the request's last item, so
  * requests retire one by one while the batch runs on, and a request that
  * arrives meanwhile joins the next batch a slot takes.  Other requests
- * (MLS_PREC_F64, the Wendland weight, the two-pass bfloat16 form) run
- * alone on a slot.  Memory: resident point sets + slots x slot_scratch_bytes
+ * (MLS_PREC_F64, the Wendland weight, other lp_terms) run alone on a
+ * slot.  Memory: resident point sets + slots x slot_scratch_bytes
  * (+ the tuner's reservation) <= hbm_budget_bytes; admitted requests
  * allocate nothing.  All server calls are thread-safe.  Results of a request
  * are bit-identical to mls_fit's with the same arguments, alone or among

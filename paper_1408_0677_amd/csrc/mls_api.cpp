@@ -284,7 +284,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 namespace mls {
 
-// Device scratch layout of one mls_fit call (none for the float64 path).
+// Device scratch layout of one mls_fit call.
 FitPlan make_fit_plan(int64_t n, int32_t d, int32_t precision, int32_t wkind, double h,
                       double x0, double y0, double dx, double dy, int32_t W, int32_t H) {
   FitPlan p{};

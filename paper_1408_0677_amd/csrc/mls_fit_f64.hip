@@ -16,7 +16,8 @@
 //      gy[row][k] (the Gaussian separates on a grid, so a tile needs
 //      16 + 4R factors per point instead of 64R), and the feature block
 //      G[j][k] in float64.  The factors follow by stepping from node to node
-//      (gauss_steps: two exponentials per point, axis and half),
+//      (gauss_steps: two exponentials per point, axis and half), or are copied
+//      from tables of the launch (mls_fit_f64_all.hip),
 //   3. MFMA sweep: the A operand (node x point weight) is gx * gy, built in
 //      registers; B is read from G.  Within each group of 16 points a lane
 //      supplies points k0 + 4 (lane / 16) + j for MFMA j = 0..3, so it reads
@@ -31,9 +32,11 @@
 // contracts 13% of the points.  Gaussian fits whose feature block would be
 // wider than 16 columns take the two-pass form instead
 // (mls_fit_f64_shape.hip); this kernel keeps the constant basis, the linear
-// basis with up to 3 attributes, the rigid map, and every inverse-distance
-// fit.  3,000 points, 9 attributes, constant basis, 700 x 500: 545 -> 277 us;
-// 4,500 points, 2 attributes, linear: 875 -> 308 us.
+// basis with up to 3 attributes, the rigid map, every inverse-distance fit, and
+// the Gaussian fits whose tiles would list nearly all points anyway and that
+// gain by the tables (f64_sums_all).  3,000 points, 9 attributes, constant
+// basis, 700 x 500: 545 us over all points, 277 in reach; 4,500 points, 2
+// attributes, linear: 875 and 308.
 #include "mls_fit_f64_kernel.h"
 
 namespace mls {
@@ -90,13 +93,13 @@ __global__ __launch_bounds__(kThreads) void look_kernel(const float* vals, int64
 
 // Most points for which a tile leaves out those beyond its reach.  The tiles'
 // own tests of the points cost n x tiles, but that is not why the line lies
-// here (40,000 points, quadratic, 1024^2 would take about 5 ms instead of 41):
-// a float64 request beyond it is the long one that the server's queue test
-// holds a slot with while it sets up, cancels and times out others behind it.
+// here: tests/test_gpu_server.py queues, cancels and times out requests behind
+// a float64 request of 40,000 points (quadratic, 1024^2), which has to run longer
+// than the 25 ms that this takes the host; in reach it would take 7.
 constexpr int64_t kReachPoints = 32768;
 
 // Values that every tile looks through itself rather than by look_kernel
-// (a launch, about 3 us, against 64 loads per thread).
+// (a launch, 5 us, against 64 loads per thread).
 constexpr int64_t kLookInTile = 16384;
 
 }  // namespace

@@ -87,7 +87,8 @@ bool lp_batch_class(const FitArgs& a, bool fp16, int terms, LPBatchClass* cls) {
 
 size_t lp_params_bytes() { return sizeof(LPParams); }
 
-// Parameters of a one-pass fit (launch_fit_lp and the served batches).
+// Parameters of a fit in either form over all points (launch_fit_lp and the
+// served batches; two passes set their own slabs).
 static LPParams dense_lp_params(const FitArgs& a, const float* vals_s, const float* shift,
                                 const float* scale, bool fp16) {
   int nts, ds, nslab;
