@@ -137,9 +137,11 @@ GAUSS_REACH = {"f64": math.sqrt(53 * math.log(2)), "bf16": math.sqrt(24 * math.l
                "fp16": math.sqrt(27.8)}
 
 # the sources that decide each contraction kernel's memory traffic
-F64_SOURCES = ["paper_1408_0677_amd/csrc/mls_fit_f64_shape.hip",
-               "paper_1408_0677_amd/csrc/mls_fit_f64.h", "paper_1408_0677_amd/csrc/mls_solve.h"]
-LP_SOURCES = ["paper_1408_0677_amd/csrc/mls_fit_lp.h", "paper_1408_0677_amd/csrc/mls_solve.h"]
+F64_SOURCES = ["paper_1408_0677_amd/csrc/" + f for f in
+               ("mls_fit_f64.hip", "mls_fit_f64_shape.hip", "mls_fit_f64.h", "mls_list.h",
+                "mls_solve.h")]
+LP_SOURCES = ["paper_1408_0677_amd/csrc/" + f for f in
+              ("mls_fit_lp.hip", "mls_fit_lp.h", "mls_list.h", "mls_solve.h")]
 
 
 def serve_bench(args):

@@ -123,19 +123,24 @@ static double reach_share(const FitArgs& a) {
   return axis(a.dx, a.W) * axis(a.dy, a.H);
 }
 
-// Past kReachPoints the line between one pass over all points, with tables, and
-// two lies where one gains as much on the calls with slopes as two on those
-// without (which take the same form, so that the fields are the same bits):
-// 30,000 points, 256^2, us one pass / two, linear d = 13 3,279 / 2,966 and with
-// slopes 3,279 / 5,350, d = 30 6,749 / 3,935 and 6,757 / 9,576; quadratic d = 4
-// 3,226 / 2,876 and 3,214 / 4,574, d = 8 4,010 / 3,128 and 4,609 / 5,257.
+// Past kReachPoints the line between one pass over all points and two lies
+// where one gains as much on the calls with slopes as two on those without
+// (which take the same form, so that the fields are the same bits).  33,000
+// points, 256^2, with tables, us one pass / two: linear d = 4 2,490 / 3,220 and
+// with slopes 2,500 / 4,160, d = 14 3,600 / 3,850 and 3,600 / 6,220, d = 30 7,630
+// / 4,940 and 7,680 / 10,900; quadratic d = 5 3,580 / 4,040 and 3,570 / 5,880,
+// d = 8 4,890 / 4,060 and 6,000 / 5,900.  Where the tables pass the scratch cap one
+// pass forms the factors in its tiles: 40,000 points, 1024^2, ms, linear d = 4
+// 44.1 / 35.6 and 44.1 / 58.9, quadratic d = 4 73.1 / 58.1 and 72.8 / 95.8, d = 8
+// 98.5 / 63.8 and 126.7 / 109.7: the same line.
 // Below it, where a call has work enough for the tables' launch and nearly all
 // points are in reach, the forms that gain by the tables' factors (3,000 points,
-// 512^2, us tables / list): constant d = 1 176 / 260, d = 60 1,675 / 1,820,
-// linear d = 2 399 / 427, quadratic d = 2 822 / 952 and with slopes 948 / 1,723;
-// linear d = 8 822 / 716, but with slopes 826 / 1,400.  (Constant d = 13 528 /
-// 491, d = 45 1,357 / 1,268, linear d = 4 816 / 621, quadratic d = 4 1,320 /
-// 957: the list.)
+// 512^2, us tables / list): constant d = 1 214 / 298, d = 60 1,674 / 1,834,
+// linear d = 2 416 / 442, d = 8 831 / 730 but with slopes 840 / 1,303, quadratic
+// d = 2 830 / 963 and with slopes 966 / 1,574.  (The others take the list:
+// constant d = 13 561 / 515, d = 45 1,368 / 1,275, linear d = 4 852 / 639 and with
+// slopes 855 / 1,038, d = 13 1,226 / 919 and 1,405 / 1,901, quadratic d = 4 1,502 /
+// 965 and 1,516 / 1,579.)
 bool f64_sums_all(const FitArgs& a) {
   if (a.wkind != 0) return false;
   const int F = moment_terms(a.degree) + basis_terms(a.degree) * a.D;

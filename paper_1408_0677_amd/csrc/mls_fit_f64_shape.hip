@@ -23,8 +23,9 @@
 // where three take 1,034).
 // 5,000 points, 13 attributes, h = 0.03, 1024^2, linear: 7,890 -> 1,030 us,
 // of which the reach gives 6.1x and the rest is this form.  Counters there:
-// matrix instructions busy 49% and vector instructions 24% of the SIMDs'
-// cycles, 35.4M matrix instructions.  3,001 points, 5 attributes, quadratic,
+// matrix instructions busy 44% and vector instructions 27% of the SIMDs'
+// cycles, 37.2M matrix instructions; 170 MB written, 56 of it the outputs and the
+// rest registers that three workgroups a unit spill.  3,001 points, 5 attributes, quadratic,
 // 517 x 389, with slopes: 1,500 -> 854 us (930 with a sweep for each output).
 #include "mls_fit_f64.h"
 
