@@ -760,6 +760,14 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
               }
             }
           }
+          // each k-step reads and multiplies by itself, the last one before the
+          // barrier: the compiler gathers both steps' LDS reads at the top
+          // otherwise, so that no matrix instruction runs under their latency, and
+          // moves the second step's past the barrier (20,000 points, us before /
+          // with this: all in reach, 256^2, float16 quadratic d = 4 695 / 600,
+          // constant d = 8 508 / 433, bfloat16 551 / 508; h = 0.05, 512^2, float16
+          // 652 / 556 and 475 / 400, bfloat16 591 / 533)
+          __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
       }
@@ -1197,6 +1205,10 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
   // The points in reach, a list at a time; `kept` is the last list, which
   // pass 2 uses again if it was the only one.
   constexpr bool ADAPT = __is_same(T, __bf16);
+  // Whether a k-step's instructions stay together, as in the one-pass form:
+  // float16 only (7,351 points, 19 attributes, 701 x 643, us without / with 550 /
+  // 530; bfloat16, 50,000 points, 64 attributes, 2048^2, 7,558 / 7,791).
+  constexpr bool kFence = __is_same(T, _Float16);
   const uint16_t* list = (const uint16_t*)(lds_sh + L::kList0);
   const TileReach reach = tile_reach(p, c0, r0, cxr, cyr);
   bool cut = ADAPT;   // the adaptive reach applies
@@ -1286,6 +1298,7 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
                 for (int t = 0; t < R; ++t) acc[t] = mfma16(alo[t], b, acc[t]);
               }
             }
+            if (kFence) __builtin_amdgcn_sched_barrier(0);
           }
           __syncthreads();
         }
@@ -1465,6 +1478,7 @@ __device__ __forceinline__ void shape_tile(const LPParams& p, int block, char* l
               acc[t][q] = mfma16(ahi[t], b2, acc[t][q]);
             }
           }
+          if (kFence) __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
       }
