@@ -638,8 +638,12 @@ __device__ __forceinline__ void make_chunk(const LPParams& p, const float* raw, 
 // One node tile and attribute slab of a fit: `block` indexes (slab, tile
 // slot) as a launch's workgroup index does.  Every thread of the workgroup
 // calls it with the same arguments.
-template <int DEG, int NTS, int S, typename T, bool WEND, bool CELLS>
-__device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_lp) {
+// Adaptive reach (bfloat16, Gaussian): the tile is summed once more without it
+// where a node could see past it.  With ONCE that is the caller's to do: `reach_on`
+// says whether the reach applies, and the result whether to call again without.
+template <int DEG, int NTS, int S, typename T, bool WEND, bool CELLS, bool ONCE = false>
+__device__ __forceinline__ bool lp_tile(const LPParams& p, int block, char* lds_lp,
+                                        bool reach_on = true) {
   using L = LPLayout<DEG, NTS, S, T>;
   typedef typename Vec8<T>::type vec8;
 
@@ -652,7 +656,7 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
   const int per_slab = CELLS ? p.slots : p.tiles;
   const int slab = block / per_slab;
   const uint32_t tile_u = CELLS ? p.torder[block % per_slab] : (uint32_t)(block % per_slab);
-  if (tile_u == 0xFFFFFFFFu) return;
+  if (tile_u == 0xFFFFFFFFu) return false;
   const int tile = (int)tile_u;
   const int c0 = (tile % p.tiles_x) * kCols;
   const int r0 = (tile / p.tiles_x) * kRows;
@@ -675,7 +679,7 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
   const TileReach reach = CELLS ? TileReach{} : tile_reach(p, c0, r0, cxr, cyr);
   // Adaptive reach: whether it still applies, and the scale it was chosen by.
   constexpr bool ADAPT = !CELLS && __is_same(T, __bf16);
-  bool cut = ADAPT;
+  bool cut = ADAPT && reach_on;
   float scale = __builtin_inff();
   auto next_list = [&](int64_t& pos, Walker& wk) {
     if (CELLS) {
@@ -778,7 +782,7 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
     // (made again where the tile is summed again: held over the solve, what
     // follows from the thread's index takes more registers than there are)
     int ptl = pt;
-    if (ADAPT) asm volatile("" : "+v"(ptl));
+    if (ADAPT && !ONCE) asm volatile("" : "+v"(ptl));
     __builtin_assume(ptl >= 0 && ptl < kProd);
     const int pt = ptl;
     float toff[kTabIt];
@@ -871,8 +875,9 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
     }
   }
   // once more without the adaptive reach where a node could see past it
-  if (!ADAPT || !cut) break;
-  if (!__syncthreads_or(low)) break;
+  if (!ADAPT || !cut) return false;
+  if (!__syncthreads_or(low)) return false;
+  if (ONCE) return true;
   cut = false;
   }
 }
@@ -880,7 +885,7 @@ __device__ __forceinline__ void lp_tile(const LPParams& p, int block, char* lds_
 template <int DEG, int NTS, int S, typename T, bool WEND, bool CELLS>
 __global__ __launch_bounds__(kThreads) void fit_lp_kernel(LPParams p) {
   extern __shared__ __attribute__((aligned(16))) char lds_lp[];
-  lp_tile<DEG, NTS, S, T, WEND, CELLS>(p, blockIdx.x, lds_lp);
+  (void)lp_tile<DEG, NTS, S, T, WEND, CELLS>(p, blockIdx.x, lds_lp);
 }
 
 // ---------------------------------------------------------------------------
@@ -1619,9 +1624,15 @@ hipError_t launch_shape_terms(const LPParams& p, int deg, int ntv, int terms, hi
 // are loaded through the scalar cache as kernel arguments are, and the
 // work area is named as the dynamic LDS array itself, so that its accesses
 // are LDS instructions rather than flat ones.
-// SHAPE: the two-pass form, NTS attribute tiles.
+// SHAPE: the two-pass form, NTS attribute tiles.  The one-pass form's second run
+// without the adaptive reach is a call as well (`reach_on`, result as lp_tile's):
+// a loop around the tile makes values of the first run live over its solve, 34 to
+// 149 spilled registers of the quadratic basis (six requests of 2,000 points, 24
+// attributes, 300^2, bfloat16 1,152 -> 1,075 us).  A direct launch, whose tile is not
+// a call otherwise, lost 4 to 10% by it.
 template <int DEG, int NTS, int S, typename T, bool SHAPE>
-__device__ __noinline__ void lp_tile_item(const LPParams* __restrict__ pp, int block) {
+__device__ __noinline__ int lp_tile_item(const LPParams* __restrict__ pp, int block,
+                                         int reach_on) {
   extern __shared__ __attribute__((aligned(16))) char lds_lp[];
   // the parameter block is written before the launch and only read by the
   // kernel: in the constant address space its loads are scalar loads that
@@ -1631,12 +1642,15 @@ __device__ __noinline__ void lp_tile_item(const LPParams* __restrict__ pp, int b
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
   typedef const __attribute__((address_space(4))) LPParams* ConstParams;
   const ConstParams pc = (ConstParams)(uintptr_t)(((uint64_t)hi << 32) | lo);
-  if constexpr (SHAPE)
+  if constexpr (SHAPE) {
     shape_tile<DEG, NTS, S, T>(*(const LPParams*)pc, __builtin_amdgcn_readfirstlane(block),
                                lds_lp);
-  else
-    lp_tile<DEG, NTS, S, T, false, false>(*(const LPParams*)pc,
-                                          __builtin_amdgcn_readfirstlane(block), lds_lp);
+    return 0;
+  } else {
+    return lp_tile<DEG, NTS, S, T, false, false, true>(
+        *(const LPParams*)pc, __builtin_amdgcn_readfirstlane(block), lds_lp,
+        __builtin_amdgcn_readfirstlane(reach_on) != 0);
+  }
 }
 
 // Thread 0 takes the next item in a branch at the top of the loop; it
@@ -1696,7 +1710,9 @@ __global__ __launch_bounds__(kThreads) void fit_lp_batch_kernel(LPBatch b) {
     if (!skip) {
       // read in place (uniform, read-only): fields are loaded where used,
       // as kernel arguments are, instead of held in registers
-      lp_tile_item<DEG, NTS, S, T, SHAPE>(b.reqs + req, block);
+      const int again = lp_tile_item<DEG, NTS, S, T, SHAPE>(b.reqs + req, block, 1);
+      if (!SHAPE && __is_same(T, __bf16) && __builtin_amdgcn_readfirstlane(again))
+        (void)lp_tile_item<DEG, NTS, S, T, SHAPE>(b.reqs + req, block, 0);
     }
     ++cur_cnt;
     __syncthreads();
